@@ -368,7 +368,8 @@ int32_t alp_eval_candidates(alp_ctx *ctx, uint32_t instance, uint32_t gpu_budget
  * before the scan (the two-launch form), also where one launch would do. */
 #define ALP_LAUNCH_SEPARATE_TERMS 16u
 
-/* Launch choices, for tests and tuning.  variant: 0 automatic, 1 row-minimum scan (default),
+/* Launch choices, for tests and tuning.  variant: 0 automatic (the packed 16-bit scan, one launch,
+ * where the space is within its ranges and large enough, else variant 1 or 6), 1 row-minimum scan,
  * 2 thread-per-candidate scan, 3 exact-tracking lane scan, 4 row-minimum scan with fixed row
  * ranges per wave, 5 row-minimum scan with rows handed out within each block (variant 1 picks
  * between the two; rows can only be split with the second, so variant 4 ignores inner_chunks),

@@ -12,6 +12,7 @@
 #include <algorithm>
 #include <array>
 #include <chrono>
+#include <cmath>
 #include <new>
 #include <vector>
 
@@ -148,6 +149,8 @@ struct alp_ctx {
     uint64_t H = 0;
     int num_cus = 0;
 
+    uint32_t max_usable = 0;       // most deployable options of the last LLM, over the instances
+    uint32_t max_units = 0;        // most share units of a deployable option
     DevBuf tables;                 // W | n | p | allowed | rate | lat
     alp::TablesDev tdev{};
 
@@ -255,8 +258,9 @@ int32_t validate_space(const alp_space_t *s, uint32_t *O_out, uint64_t *N_out)
 
 int32_t validate_tables(const alp_space_t *s, uint32_t B, const uint64_t *W, const uint32_t *n,
                         const uint32_t *p, const uint8_t *allowed, const uint32_t *rate,
-                        const uint32_t *lat, uint64_t H)
+                        const uint32_t *lat, uint64_t H, uint32_t *max_usable, uint32_t *max_units)
 {
+    *max_usable = *max_units = 0;
     if (!W || !n || !p || !allowed || !rate || !lat)
         return fail(ALP_EINVAL, "a table pointer is NULL");
     if (H < 1 || H >= (UINT64_C(1) << 48))
@@ -271,6 +275,7 @@ int32_t validate_tables(const alp_space_t *s, uint32_t B, const uint64_t *W, con
             if (n[lm] < 1 || n[lm] >= (1u << 31) || p[lm] < 1 || p[lm] >= (1u << 31))
                 return fail(ALP_EINVAL, "instance %u llm %u: n_milli/p_milli outside 1..2^31-1", b, m);
             uint64_t worst_m = 0;
+            uint32_t usable_m = 0;
             for (uint32_t i = 0; i < nt; ++i) {
                 for (uint32_t j = 0; j < nf; ++j) {
                     const uint64_t tab = (lm * nt + i) * nf + j;
@@ -292,9 +297,14 @@ int32_t validate_tables(const alp_space_t *s, uint32_t B, const uint64_t *W, con
                     if (allowed[tab] && fits) {
                         const uint64_t c = (uint64_t)max_lat * n[lm] / p[lm];
                         worst_m = c > worst_m ? c : worst_m;
+                        usable_m += s->max_replicas;
+                        *max_units = std::max(*max_units, s->tp_values[i] * s->frac_units[j] *
+                                                              s->max_replicas);
                     }
                 }
             }
+            if (m == M - 1)
+                *max_usable = std::max(*max_usable, usable_m);
             worst += worst_m;
             if (worst >= 0xFFFFFFFFull)
                 return fail(ALP_ERANGE,
@@ -354,6 +364,165 @@ uint64_t blocks_per_item_for_rounds(uint64_t count, uint64_t resident, uint64_t 
     return best;
 }
 
+// The packed scan's plan (alp_packed.hip), if the space is within its 16-bit ranges: ranks below S
+// and scaled units up to (U + 1) * S within 16 bits (the signed form, one minimum per two records:
+// below the half-precision infinity's pattern), sums of the other LLMs' units below the unusable
+// option's, and the block's tables in LDS.
+//
+// Where the masked scan stays (both measured, us per queued search; packed against masked): its
+// blocks need no ranks and start sooner, which decides among the smallest searches.  With two LLMs
+// it is the better one unless many items have options for more than two slots a lane (O = 128:
+// 7.8 against 6.7 for one item, 13.8 against 12.8 for 1,000; O = 156 with 1,000 items: 16.5 against
+// 24.5).  With three, for a few items of 64 options and more (one item: O = 64 9.0 against 8.9, O =
+// 128 10.2 against 9.3, O = 256 13.2 against 11.9; eight items of O = 128: 10.7 against 11.2; O =
+// 48: 8.4 against 8.9).
+bool plan_packed(const alp_ctx *c, uint32_t count, alp::ScanGeometry &out)
+{
+    const alp::SpaceDev &sp = c->sp;
+    if (sp.M < 2 || sp.O < 2)
+        return false;
+    if (sp.M == 2 && (sp.O <= 128 || count < (UINT64_C(1) << 24) / c->N))
+        return false;
+    if (sp.M == 3 && sp.O >= 64 && count < 8)
+        return false;
+    uint32_t unit = 0;
+    for (uint32_t j = 0; j < sp.n_fq; ++j)
+        for (uint32_t a = sp.fq(j), b = unit;;) {       // Euclid
+            if (b == 0) {
+                unit = a;
+                break;
+            }
+            const uint32_t r = a % b;
+            a = b;
+            b = r;
+        }
+    alp::ScanGeometry g{};
+    alp::PackedPlan &p = g.packed;
+    p.S = std::max<uint32_t>(1, c->max_usable);
+    p.U = std::max<uint32_t>(1, c->max_units / unit);
+    p.mul_unit = alp::div_multiplier(unit);
+    p.mul_fq = alp::div_multiplier(sp.n_fq);
+    p.inv_O = 0xFFFFFFFFu / sp.O;
+    p.wide_index = c->N / sp.O >= (UINT64_C(1) << 32) ? 1u : 0u;
+    const uint64_t range = ((uint64_t)p.U + 1) * p.S;
+    if (range > 0xFFFF || (uint64_t)p.U * sp.M >= 0x7FFF ||
+        alp::packed_lds_bytes(sp, p.S) > (UINT64_C(56) << 10))
+        return false;
+    p.wide = range >= 0x7C00 ? 1u : 0u;
+    p.E = sp.M > 2 ? sp.O * sp.O : sp.O;
+    p.rows = 1;
+    for (uint32_t m = 3; m < sp.M; ++m)
+        p.rows *= sp.O;
+    // Registers of pairs per lane: four, each record then feeding 8 pairs, unless that leaves
+    // fewer tiles than fill the chip twice (two, then one).
+    const uint64_t items = std::max<uint64_t>(1, count);
+    const uint64_t cus = c->num_cus > 0 ? (uint64_t)c->num_cus : 256;
+    auto tiles = [&](uint32_t r) { return p.rows * ceil_div(p.E, 128 * r); };
+    g.slots = items * tiles(4) >= 8 * cus ? 4 : items * tiles(2) >= 4 * cus ? 2 : 1;
+    while (g.slots > 1 && 128 * (g.slots / 2) >= p.E)
+        g.slots /= 2;
+    p.chunks = (uint32_t)ceil_div(p.E, 128 * g.slots);
+    const uint64_t own = tiles(g.slots), total = items * own;
+    // Waves of a block that owns whole rows: the count up to 16 that leaves the fewest idle over
+    // the chunks (the larger of equals); `phases` of them share a chunk's rows.
+    uint32_t row_waves = 16;
+    auto idle = [&](uint32_t k) {
+        const uint64_t use = p.chunks >= k ? ceil_div(p.chunks, k) * k : k;
+        return (double)use / (double)(p.chunks >= k ? p.chunks : k / p.chunks * p.chunks);
+    };
+    for (uint32_t k = 15; k >= 8; --k)
+        if (idle(k) < idle(row_waves) - 1e-9)
+            row_waves = k;
+    const uint64_t phases = p.chunks < row_waves ? row_waves / p.chunks : 1;
+    // A tile's instructions, those of the lanes' set-up and of finding the row (measured shares),
+    // and a block's prologue.
+    const double tile = 2.5 * g.slots * alp::inner_stride(sp.O) + 13.0 * g.slots + 45.0;
+    const double setup = (sp.O % 64 == 0 ? 6.0 : 12.0) * g.slots + (sp.M > 3 ? 90.0 : 20.0);
+    constexpr double kPrologue = 5600.0;
+    uint64_t bpi = 1;
+    bool by_rows = own >= (UINT64_C(1) << 31);
+    if (c->bpi_override) {
+        bpi = std::min<uint64_t>(c->bpi_override, own);
+        by_rows = by_rows || p.rows >= 4 * bpi * phases;
+    } else if (total >= 32 * cus) {
+        // Two tiles a wave and more: of the block counts up to a multiple of those resident (32
+        // waves a CU), the least cost by the instructions issued, times the CU with the most
+        // blocks against the mean (a CU's blocks share its issue whether they run together or in
+        // turn), and a fortieth of a round for the waves that end last on emptying SIMDs.
+        double least = 1e300;
+        for (int rows = 0; rows < 2; ++rows) {
+            const uint64_t w = rows ? row_waves : 16, resident = cus * (32 / w);
+            if ((by_rows && !rows) || (rows && p.rows < 4 * phases))
+                continue;
+            for (uint64_t k = 1; k <= 16; ++k) {
+                uint64_t n = std::max<uint64_t>(1, std::min(k * resident / items, own));
+                double issued;
+                if (rows) {
+                    n = std::min(n, p.rows);
+                    const uint64_t per = ceil_div(p.rows, n), wave_rows = ceil_div(per, phases);
+                    n = ceil_div(p.rows, per);
+                    issued = (double)(n * w) * (double)ceil_div(p.chunks, w) *
+                             (setup + tile * (double)wave_rows);
+                } else {
+                    const uint64_t per = ceil_div(own, n);
+                    n = ceil_div(own, per);
+                    issued = (double)(n * w) * (double)ceil_div(per, w) * (setup + tile);
+                }
+                const double per_cu = (double)(n * items) / (double)cus;
+                const double cost = (issued + kPrologue * (double)n) *
+                                    (std::ceil(per_cu) / per_cu +
+                                     0.025 * (double)resident / (double)(n * items));
+                if (cost < least) {
+                    least = cost;
+                    bpi = n;
+                    by_rows = rows != 0;
+                }
+            }
+        }
+    } else if (total >= 16 * cus) {
+        bpi = cus / items;                             // a block of 16 waves on each CU
+    } else {
+        // Small searches: a block for every 16 groups of 16 records by 128 pairs.
+        const uint64_t groups = items * tiles(1) * (alp::inner_stride(sp.O) / 16);
+        bpi = std::min(cus, groups / 16) / items;
+    }
+    bpi = std::max<uint64_t>(1, std::min(bpi, by_rows ? p.rows : own));
+    uint32_t w = row_waves;
+    if (by_rows) {
+        p.rows_per_block = ceil_div(p.rows, bpi);
+        bpi = ceil_div(p.rows, p.rows_per_block);
+    } else {
+        p.rows_per_block = 0;
+        p.tiles = (uint32_t)own;
+        p.tiles_per_block = (uint32_t)ceil_div(own, bpi);
+        bpi = ceil_div(own, p.tiles_per_block);
+        // 16 waves for one of several blocks with as many tiles; else the count up to 12 that
+        // leaves the fewest idle in the last pass over the block's tiles (8 first), or whole
+        // multiples of fewer tiles.
+        const uint32_t n = p.tiles_per_block;
+        if (bpi > 1 && n >= 16) {
+            w = 16;
+        } else if (n < 8) {
+            w = n * (8 / n);
+        } else {
+            w = 8;
+            for (uint32_t k : {7u, 6u, 5u, 4u, 9u, 10u, 11u, 12u})
+                if (ceil_div(n, k) * k < ceil_div(n, w) * w)
+                    w = k;
+        }
+    }
+    if (bpi * items >= (UINT64_C(1) << 31))
+        return false;
+    g.blocks_per_item = (uint32_t)bpi;
+    g.threads = c->tpb_override ? c->tpb_override : 64 * w;
+    g.variant = 1;
+    g.rows = p.rows;
+    g.fused = 1;
+    g.use_packed = 1;
+    out = g;
+    return true;
+}
+
 // Launch geometry of a scan of `count` items.  ERANGE when no launch can cover the space: the
 // fixed-range form counts a wave's rows in 32 bits, so a wave must get fewer than 2^32 rows
 // (the automatic plan adds blocks until it does; a blocks_per_item override that leaves a wave
@@ -365,6 +534,8 @@ int32_t plan_scan(alp_ctx *c, uint32_t count, alp::ScanGeometry &out, bool allow
 {
     alp::ScanGeometry g{};
     const alp::SpaceDev &sp = c->sp;
+    if (c->variant == 0 && allow_fused && !c->chunks_override && plan_packed(c, count, out))
+        return ALP_OK;
     // Variants 4 and 5 are the row-minimum scan with a fixed choice of work distribution;
     // ALP_LAUNCH_SEPARATE_TERMS added to 0, 1, 4 or 5 keeps the option terms in their own kernel.
     const uint32_t variant = c->variant & ~ALP_LAUNCH_SEPARATE_TERMS;
@@ -607,6 +778,7 @@ struct SearchScratch {
     uint2 *regions = nullptr;                  // one-launch form
     uint32_t *fdone = nullptr, *fgroup = nullptr;
     unsigned long long *fbest = nullptr;
+    unsigned long long *slots = nullptr;       // packed scan
 };
 
 // Byte sizes of the scratch parts of a launch of `count` items with geometry g.  done[count],
@@ -635,9 +807,24 @@ int32_t context_scratch(alp_ctx *c, uint32_t count, const alp::ScanGeometry &g, 
     if (g.fused) {
         // Per block: its option records; per item: the best word (8 B), then the counters.
         const uint64_t blocks = (uint64_t)count * g.blocks_per_item;
-        if ((e = c->fused_regions.ensure(blocks * alp::fused_region(c->sp.M, c->sp.O) *
-                                         sizeof(uint2))) != hipSuccess)
+        const uint64_t region = g.use_packed
+                                    ? alp::inner_stride(c->sp.O) * sizeof(uint32_t)
+                                    : alp::fused_region(c->sp.M, c->sp.O) * sizeof(uint2);
+        if ((e = c->fused_regions.ensure(blocks * region)) != hipSuccess)
             return hip_fail(e, "hipMalloc(block records)");
+        if (g.use_packed) {
+            const uint64_t lines = 1 + ceil_div(g.blocks_per_item, alp::kPackedGroup);
+            if (g.blocks_per_item > 1 &&
+                ((e = c->winners.ensure(blocks * (g.packed.wide_index ? 2 : 1) * sizeof(uint64_t))) !=
+                     hipSuccess ||
+                 (e = c->fused_words.ensure(count * lines * alp::kPackedLine *
+                                            sizeof(uint32_t))) != hipSuccess))
+                return hip_fail(e, "hipMalloc(item words)");
+            s.regions = (uint2 *)c->fused_regions.ptr;
+            s.slots = (unsigned long long *)c->winners.ptr;
+            s.fgroup = (uint32_t *)c->fused_words.ptr;
+            return ALP_OK;
+        }
         const uint64_t groups = (g.blocks_per_item + alp::kFusedGroup - 1) / alp::kFusedGroup;
         if ((e = c->fused_words.ensure((uint64_t)count * (12 + 4 * groups))) != hipSuccess)
             return hip_fail(e, "hipMalloc(item words)");
@@ -699,6 +886,15 @@ int32_t launch_search_with(alp_ctx *c, const alp::QueryDev &q, uint32_t count, a
         fz.done = s.fdone;
         fz.group_done = s.fgroup;
         fz.best = s.fbest;
+        fz.slots = s.slots;
+        if (g.use_packed) {
+            if ((e = alp::launch_packed(sp, q, count, g, fa, fz, c->stream,
+                                        timed ? ev[2] : nullptr, timed ? ev[3] : nullptr)) !=
+                hipSuccess)
+                return hip_fail(e, "scan launch");
+            c->last_blocks = (uint32_t)nwin;
+            return ALP_OK;
+        }
         if ((e = alp::launch_scan(sp, q, count, nullptr, nullptr, g, nullptr, fa, c->stream,
                                   timed ? ev[2] : nullptr, timed ? ev[3] : nullptr, &fz)) !=
             hipSuccess)
@@ -856,8 +1052,9 @@ int32_t alp_load_profiles(alp_ctx **out, const alp_space_t *space, uint32_t num_
         return st;
     if (num_instances < 1)
         return fail(ALP_EINVAL, "num_instances must be >= 1");
+    uint32_t max_usable = 0, max_units = 0;
     st = validate_tables(space, num_instances, weight_bytes, n_milli, p_milli, allowed, rate_milli,
-                         lat_us, hbm_bytes_per_gpu);
+                         lat_us, hbm_bytes_per_gpu, &max_usable, &max_units);
     if (st != ALP_OK)
         return st;
 
@@ -886,6 +1083,8 @@ int32_t alp_load_profiles(alp_ctx **out, const alp_space_t *space, uint32_t num_
     c->N = N;
     c->B = num_instances;
     c->H = hbm_bytes_per_gpu;
+    c->max_usable = max_usable;
+    c->max_units = max_units;
     alp::SpaceDev &sp = c->sp;
     sp.M = space->num_llms;
     sp.n_tp = space->num_tp;

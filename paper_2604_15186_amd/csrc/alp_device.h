@@ -181,21 +181,22 @@ __device__ __forceinline__ uint32_t candidate_digit(const SpaceDev &sp, uint64_t
 }
 
 // The result record of winner (L, x) written as the six 64-bit words of alp_result_t, by all
-// lanes of one wave with the same (L, x): lane m < M holds LLM m's option o, its normalised
-// throughput T (Eq. 2 term) and share units U; the wave takes T_w as their minimum (Eq. 2) and
-// sums U, and lane 0 writes.
-__device__ __forceinline__ void write_result_lanes(const SpaceDev &sp, uint32_t o, uint32_t T,
-                                                   uint32_t U, uint32_t L, uint64_t x,
-                                                   uint64_t *dst, uint32_t status_if_none,
+// lanes of one wave with the same (L, x): lane m < M holds LLM m's option o (its (tp, share)
+// pair ij = o / D and the pair's indices i = ij / n_fq and j), its normalised throughput T (Eq. 2
+// term) and share units U; the wave takes T_w as their minimum (Eq. 2) and sums U, and lane 0
+// writes.
+__device__ __forceinline__ void write_result_lanes(const SpaceDev &sp, uint32_t o, uint32_t ij,
+                                                   uint32_t i, uint32_t T, uint32_t U, uint32_t L,
+                                                   uint64_t x, uint64_t *dst,
+                                                   uint32_t status_if_none,
                                                    uint32_t *signal = nullptr, uint32_t seq = 0)
 {
     const uint32_t lane = threadIdx.x & 63;
     uint64_t tp = 0, fq = 0, rep = 0;
     if (L != kNoLatency && lane < sp.M) {
-        const uint32_t ij = o / sp.D;
-        tp = (uint64_t)sp.tp(ij / sp.n_fq) << (8 * lane);
-        fq = (uint64_t)sp.fq(ij % sp.n_fq) << (8 * lane);
-        rep = (uint64_t)((o % sp.D + 1) & 0xFFu) << (8 * lane);
+        tp = (uint64_t)sp.tp(i) << (8 * lane);
+        fq = (uint64_t)sp.fq(ij - i * sp.n_fq) << (8 * lane);
+        rep = (uint64_t)((o - ij * sp.D + 1) & 0xFFu) << (8 * lane);
     } else {
         T = 0xFFFFFFFFu;
         U = 0;
@@ -248,7 +249,8 @@ __device__ __forceinline__ void write_result(const SpaceDev &sp, const uint2 *E,
         T = e.x;
         U = e.y & 0xFFFFu;
     }
-    write_result_lanes(sp, o, T, U, L, x, dst, status_if_none, signal, seq);
+    write_result_lanes(sp, o, o / sp.D, o / sp.D / sp.n_fq, T, U, L, x, dst, status_if_none, signal,
+                       seq);
 }
 
 // Result record of one item whose winner is (L, x), by one wave.  E: the item's per-option
@@ -568,7 +570,8 @@ __device__ __forceinline__ void write_fused_result(const FinishArgs &fa, const F
         T = e.x;
         U = e.y;
     }
-    write_result_lanes(sp, o, T, U, L, x, reinterpret_cast<uint64_t *>(fa.out + item),
+    write_result_lanes(sp, o, o / sp.D, o / sp.D / sp.n_fq, T, U, L, x,
+                       reinterpret_cast<uint64_t *>(fa.out + item),
                        rejected ? (uint32_t)ALP_EINVAL : (uint32_t)ALP_INFEASIBLE, fa.signal,
                        fa.seq);
 }
@@ -655,6 +658,86 @@ __device__ __forceinline__ void load_query(const QueryDev &q, uint32_t i, uint32
         cap = q.cap1;
         lambda = q.lambda1;
     }
+}
+
+// Item `item`'s query from the device queries (raw.budget set; an instance out of range is searched
+// as instance 0 and rejected) or the prepared ones.
+__device__ __forceinline__ void load_item_query(const RawQueries &raw, const QueryDev &q,
+                                                uint32_t item, uint32_t &inst, uint32_t &cap,
+                                                uint32_t &lambda, bool &rejected)
+{
+    rejected = false;
+    if (raw.budget) {
+        // budget and target read first: the instance's read is conditional, and a
+        // conditional read is waited for where the paths join
+        const uint64_t c64 = (uint64_t)raw.units_per_gpu * raw.budget[item];
+        lambda = raw.target[item];
+        inst = raw.inst ? raw.inst[item] : item;
+        rejected = inst >= raw.B;
+        inst = rejected ? 0u : inst;
+        cap = c64 > kCapacityMax ? kCapacityMax : (uint32_t)c64;
+    } else {
+        load_query(q, item, inst, cap, lambda);
+    }
+}
+
+// The item's profile curves (one per LLM, tp and share; shared by the replica counts) staged in
+// LDS by one load per point, all in flight together, the rates padded to ALP_MAX_POINTS points
+// with the last one; each curve's deployability, tp * q of every pair, each LLM's inputs and the
+// reciprocals of 1000 d.  By the whole block; ends with its barrier.
+__device__ __forceinline__ void stage_item_tables(const SpaceDev &sp, const TablesDev &tb,
+                                                  uint32_t M, uint32_t inst, uint32_t wave,
+                                                  uint32_t *s_rate, uint32_t *s_lat,
+                                                  uint8_t *s_deploy, uint32_t *s_tpq,
+                                                  LlmInputs *s_llm, double *s_inv_dd)
+{
+    const uint32_t K = sp.K, curves = M * sp.n_tp * sp.n_fq, pairs = sp.n_tp * sp.n_fq;
+    const uint64_t base = (uint64_t)inst * curves;
+    // Stores point a (rate padded past K - 1).
+    const uint64_t lm0 = (uint64_t)inst * M;
+    auto put_point = [&](uint32_t a, uint32_t rate, uint32_t lat) {
+        const uint32_t c = a / K, k = a - c * K;
+        s_lat[a] = lat;
+        s_rate[c * ALP_MAX_POINTS + k] = rate;
+        if (k == K - 1)
+            for (uint32_t kk = K; kk < ALP_MAX_POINTS; ++kk)
+                s_rate[c * ALP_MAX_POINTS + kk] = rate;
+    };
+    // tp and q of curve (or pair) a.
+    auto curve_tp = [&](uint32_t a) { return sp.tp(a % pairs / sp.n_fq); };
+    auto curve_fq = [&](uint32_t a) { return sp.fq(a % pairs % sp.n_fq); };
+    // Every thread's first point, curve, pair and LLM are read together, at indices clamped
+    // into the item's tables (a thread past the end reads the last entry and stores
+    // nothing), so that the reads are in flight at once; further points and curves (blocks
+    // smaller than the item's tables) follow.  Waves past every table (points are the most
+    // entries, but for the D reciprocals) skip it.
+    const uint32_t points = curves * K;
+    if (wave * 64 < (points > sp.D ? points : sp.D)) {
+        const uint32_t t = threadIdx.x;
+        const uint32_t ap = t < points ? t : points - 1, ac = t < curves ? t : curves - 1;
+        const uint32_t am = t < M ? t : M - 1;
+        const uint32_t rate = tb.rate[base * K + ap], lat = tb.lat[base * K + ap];
+        const uint8_t allowed = tb.allowed[base + ac];
+        const uint64_t W = tb.W[lm0 + ac / pairs];
+        const uint32_t n = tb.n[lm0 + am], p = tb.p[lm0 + am];
+        const uint32_t tp = curve_tp(ac), fq = curve_fq(ac);
+        if (t < sp.D)
+            s_inv_dd[t] = recip_low<1, 40>(1000u * (t + 1));
+        if (t < points)
+            put_point(t, rate, lat);
+        if (t < curves)
+            s_deploy[t] = deployable(sp, tb.H, allowed != 0, W, tp * fq);
+        if (t < pairs)
+            s_tpq[t] = tp * fq;                  // curve t < pairs is pair t's
+        if (t < M)
+            s_llm[t] = llm_inputs(n, p);
+    }
+    for (uint32_t a = threadIdx.x + blockDim.x; a < curves * K; a += blockDim.x)
+        put_point(a, tb.rate[base * K + a], tb.lat[base * K + a]);
+    for (uint32_t a = threadIdx.x + blockDim.x; a < curves; a += blockDim.x)
+        s_deploy[a] = deployable(sp, tb.H, tb.allowed[base + a] != 0, tb.W[lm0 + a / pairs],
+                                 curve_tp(a) * curve_fq(a));
+    __syncthreads();
 }
 
 }  // namespace

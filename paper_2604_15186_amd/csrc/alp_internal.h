@@ -103,6 +103,20 @@ struct FinishArgs {
     uint32_t seq = 0;
 };
 
+// Tiles and scales of the packed scan (alp_packed.hip).  Share units are counted in multiples of
+// the greatest common divisor of the space's shares (mul_unit divides by it).
+struct PackedPlan {
+    uint32_t S;                // above every rank of the inner LLM's usable options
+    uint32_t U;                // most units a deployable option uses
+    uint32_t mul_unit, mul_fq; // multipliers of div_by() for that divisor and the share count
+    uint32_t inv_O;            // floor((2^32 - 1) / O)
+    uint32_t wide_index;       // lanes' indices (rows * E of them) need more than 32 bits
+    uint32_t wide;             // (U + 1) * S needs the unsigned form
+    uint32_t E, chunks;        // lane pairs, and chunks of 128 * slots of them
+    uint32_t tiles, tiles_per_block;   // rows_per_block = 0: tiles of an item, and of a block
+    uint64_t rows, rows_per_block;     // rows_per_block > 0: a block owns whole rows
+};
+
 // Launch geometry of one scan.
 struct ScanGeometry {
     uint32_t variant;          // 1: row-minimum, 2: thread-per-candidate, 3: exact-tracking lanes
@@ -121,6 +135,8 @@ struct ScanGeometry {
     uint32_t fused;            // variant 1: one launch -- every block computes its item's option
                                // terms itself, and the item's winner is one 64-bit word (spaces of
                                // fewer than 2^32 candidates, never with the pair table)
+    uint32_t use_packed;       // the packed scan instead (slots: registers of two pairs per lane)
+    PackedPlan packed;
 };
 
 // Queries of a search batch given in device memory, prepared by the option-term kernel: item i
@@ -147,7 +163,11 @@ struct FusedArgs {
     uint32_t *done;            // per item: finished block groups
     uint32_t *group_done;      // per item and group of kFusedGroup blocks: finished blocks
     unsigned long long *best;
+    unsigned long long *slots; // packed scan: per block, its lowest (latency, lanes' index)
 };
+// Packed scan: blocks counted together, and the distance of its counters in 32-bit words (an item
+// has one for its groups, then one per group, in group_done).
+constexpr uint32_t kPackedGroup = 16, kPackedLine = 32;
 // Blocks of an item counted together before the item's count (two-level counting, so that at
 // most this many blocks update one counter word).
 constexpr uint32_t kFusedGroup = 64;
@@ -211,6 +231,24 @@ __host__ __device__ inline uint32_t fused_region(uint32_t M, uint32_t O)
 {
     return (M * O + inner_stride(O) + 7u) & ~7u;    // 64-byte multiple
 }
+// Dynamic LDS of a packed scan block: the curves and deployability flags as above, the inner
+// LLM's terms (inner_stride(O) words), every option's (tau, share units) and (term, units), and
+// the term of each rank.
+__host__ __device__ inline size_t packed_lds_key_offset(const SpaceDev &sp)
+{
+    return (fused_lds_deploy_offset(sp) + fused_lds_curves(sp) + 15) & ~(size_t)15;
+}
+__host__ __device__ inline size_t packed_lds_ext_offset(const SpaceDev &sp)
+{
+    return packed_lds_key_offset(sp) + (size_t)inner_stride(sp.O) * 4;
+}
+__host__ __device__ inline size_t packed_lds_bytes(const SpaceDev &sp, uint32_t S)
+{
+    return packed_lds_ext_offset(sp) + (size_t)sp.M * sp.O * 16 + ((size_t)S + 1) * 4;
+}
+hipError_t launch_packed(const SpaceDev &sp, const QueryDev &q, uint32_t count,
+                         const ScanGeometry &g, const FinishArgs &fa, const FusedArgs &fz,
+                         hipStream_t st, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
 hipError_t launch_eval(const SpaceDev &sp, uint32_t capacity, const uint2 *rec, const uint2 *ext,
                        const uint64_t *idx, uint64_t count, alp_eval_t *out, hipStream_t st);
 hipError_t launch_tmax(const SpaceDev &sp, const QueryDev &q, uint32_t count, const uint2 *ext,

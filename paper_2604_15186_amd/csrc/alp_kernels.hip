@@ -545,32 +545,14 @@ scan_min_kernel(const uint2 *__restrict__ rec, const uint2 *__restrict__ inner_a
     __shared__ uint32_t s_tpq[FUSED ? ALP_MAX_TP * ALP_MAX_FRAC : 1];
     __shared__ double s_inv_dd[FUSED ? ALP_MAX_REPLICAS : 1];
     if constexpr (FUSED) {
-        uint32_t cap;
-        if (fz.raw.budget) {
-            // budget and target read first: the instance's read is conditional, and a
-            // conditional read is waited for where the paths join
-            const uint64_t c64 = (uint64_t)fz.raw.units_per_gpu * fz.raw.budget[item];
-            f_lambda = fz.raw.target[item];
-            f_inst = fz.raw.inst ? fz.raw.inst[item] : item;
-            f_rejected = f_inst >= fz.raw.B;
-            f_inst = f_rejected ? 0u : f_inst;
-            cap = c64 > kCapacityMax ? kCapacityMax : (uint32_t)c64;
-        } else {
-            uint32_t lam;
-            load_query(q, item, f_inst, cap, lam);
-            f_lambda = lam;
-        }
+        uint32_t cap, lam;
+        load_item_query(fz.raw, q, item, f_inst, cap, lam, f_rejected);
+        f_lambda = lam;
         capacity = (int32_t)cap;
         uint2 *blk = fz.regions + (uint64_t)blockIdx.x * fz.region;
         uint2 *blk_inner = blk + M * O;
         const uint32_t stride = inner_stride(O);
-        // The item's profile curves (one per LLM, tp and share; shared by the replica counts)
-        // staged in LDS by one load per point, all in flight together, the rates padded to
-        // ALP_MAX_POINTS points with the last one; each curve's deployability, tp * q of every
-        // pair, each LLM's inputs and the reciprocals of 1000 d.
         const SpaceDev &sp = fa.sp;
-        const uint32_t K = sp.K, curves = M * sp.n_tp * sp.n_fq, pairs = sp.n_tp * sp.n_fq;
-        const uint64_t base = (uint64_t)f_inst * curves;
         uint8_t *s_base = reinterpret_cast<uint8_t *>(s_dyn);
         uint32_t *s_rate = reinterpret_cast<uint32_t *>(s_base);
         uint32_t *s_lat = reinterpret_cast<uint32_t *>(s_base + fused_lds_lat_offset(sp));
@@ -579,51 +561,8 @@ scan_min_kernel(const uint2 *__restrict__ rec, const uint2 *__restrict__ inner_a
         uint2 *s_ext_w = reinterpret_cast<uint2 *>(s_base + fused_lds_ext_offset(sp));
         flds = FusedLds{s_rate, s_lat, s_deploy, s_tpq, s_llm, s_inv_dd, s_ext_w};
         s_inner = s_inner_w;
-        // Stores point a (rate padded past K - 1).
-        const uint64_t lm0 = (uint64_t)f_inst * M;
-        auto put_point = [&](uint32_t a, uint32_t rate, uint32_t lat) {
-            const uint32_t c = a / K, k = a - c * K;
-            s_lat[a] = lat;
-            s_rate[c * ALP_MAX_POINTS + k] = rate;
-            if (k == K - 1)
-                for (uint32_t kk = K; kk < ALP_MAX_POINTS; ++kk)
-                    s_rate[c * ALP_MAX_POINTS + kk] = rate;
-        };
-        // tp and q of curve (or pair) a.
-        auto curve_tp = [&](uint32_t a) { return sp.tp(a % pairs / sp.n_fq); };
-        auto curve_fq = [&](uint32_t a) { return sp.fq(a % pairs % sp.n_fq); };
-        // Every thread's first point, curve, pair and LLM are read together, at indices clamped
-        // into the item's tables (a thread past the end reads the last entry and stores
-        // nothing), so that the reads are in flight at once; further points and curves (blocks
-        // smaller than the item's tables) follow.  Waves past every table (points are the most
-        // entries, but for the D reciprocals) skip it.
-        const uint32_t points = curves * K;
-        if (wave * 64 < (points > sp.D ? points : sp.D)) {
-            const uint32_t t = threadIdx.x;
-            const uint32_t ap = t < points ? t : points - 1, ac = t < curves ? t : curves - 1;
-            const uint32_t am = t < M ? t : M - 1;
-            const uint32_t rate = fz.tb.rate[base * K + ap], lat = fz.tb.lat[base * K + ap];
-            const uint8_t allowed = fz.tb.allowed[base + ac];
-            const uint64_t W = fz.tb.W[lm0 + ac / pairs];
-            const uint32_t n = fz.tb.n[lm0 + am], p = fz.tb.p[lm0 + am];
-            const uint32_t tp = curve_tp(ac), fq = curve_fq(ac);
-            if (t < sp.D)
-                s_inv_dd[t] = recip_low<1, 40>(1000u * (t + 1));
-            if (t < points)
-                put_point(t, rate, lat);
-            if (t < curves)
-                s_deploy[t] = deployable(sp, fz.tb.H, allowed != 0, W, tp * fq);
-            if (t < pairs)
-                s_tpq[t] = tp * fq;                  // curve t < pairs is pair t's
-            if (t < M)
-                s_llm[t] = llm_inputs(n, p);
-        }
-        for (uint32_t a = threadIdx.x + blockDim.x; a < curves * K; a += blockDim.x)
-            put_point(a, fz.tb.rate[base * K + a], fz.tb.lat[base * K + a]);
-        for (uint32_t a = threadIdx.x + blockDim.x; a < curves; a += blockDim.x)
-            s_deploy[a] = deployable(sp, fz.tb.H, fz.tb.allowed[base + a] != 0,
-                                     fz.tb.W[lm0 + a / pairs], curve_tp(a) * curve_fq(a));
-        __syncthreads();
+        stage_item_tables(sp, fz.tb, M, f_inst, wave, s_rate, s_lat, s_deploy, s_tpq, s_llm,
+                          s_inv_dd);
         for (uint32_t a = threadIdx.x; a < M * O; a += blockDim.x) {
             const uint32_t m = div_by(a, sp.mul_O), o = a - m * O;
             const OptionTerm t = flds.term(sp, m, o, (uint32_t)f_lambda);

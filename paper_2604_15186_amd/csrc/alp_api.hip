@@ -160,7 +160,7 @@ struct alp_ctx {
     DevBuf fused_words;                     // one-launch scan: per-item best word and counter,
                                             // 0 between launches
     DevBuf split_dp;                        // allocate_kernel's knapsack table
-    DevBuf pruned_table, pruned_orders, pruned_counts;   // pruned search scratch
+    DevBuf pruned_table;                    // pruned search: option tables too large for LDS
     DevBuf place_in, place_out;                          // placement records
     alp_pruned_t *host_pruned = nullptr;    // mapped pinned results of pruned searches
     alp_pruned_t *host_pruned_dev = nullptr;
@@ -813,11 +813,10 @@ int32_t context_scratch(alp_ctx *c, uint32_t count, const alp::ScanGeometry &g, 
         if ((e = c->fused_regions.ensure(blocks * region)) != hipSuccess)
             return hip_fail(e, "hipMalloc(block records)");
         if (g.use_packed) {
-            const uint64_t lines = 1 + ceil_div(g.blocks_per_item, alp::kPackedGroup);
             if (g.blocks_per_item > 1 &&
                 ((e = c->winners.ensure(blocks * (g.packed.wide_index ? 2 : 1) * sizeof(uint64_t))) !=
                      hipSuccess ||
-                 (e = c->fused_words.ensure(count * lines * alp::kPackedLine *
+                 (e = c->fused_words.ensure(alp::block_counter_words(count, g.blocks_per_item) *
                                             sizeof(uint32_t))) != hipSuccess))
                 return hip_fail(e, "hipMalloc(item words)");
             s.regions = (uint2 *)c->fused_regions.ptr;
@@ -1509,8 +1508,7 @@ int32_t alp_search_pruned(alp_ctx *ctx, uint32_t count, const uint32_t *instance
     // the bound grows with the number of units: checking the largest query covers all
     if (pruned_vector_bound(F_max, sp.M, flags & ALP_PRUNE_ORDER) > ALP_PRUNED_MAX_VECTORS)
         return fail(ALP_ERANGE, "Q*G = %u: more than 2^34 fraction vectors per query", F_max);
-    const uint64_t F1 = (uint64_t)F_max + 1;
-    const uint32_t bpi = (uint32_t)ceil_div(alp::pruned_prefixes(sp.M, F_max), 256);
+    const uint32_t bpi = alp::pruned_blocks_per_item(sp.M, F_max, count);
     const uint64_t nblocks = (uint64_t)count * bpi;
     if (nblocks >= (UINT64_C(1) << 31))
         return fail(ALP_ERANGE, "batch too large for one launch (%llu blocks)",
@@ -1522,12 +1520,12 @@ int32_t alp_search_pruned(alp_ctx *ctx, uint32_t count, const uint32_t *instance
     const uint64_t items_bytes = (uint64_t)count * sp.M * sp.O * sizeof(uint2);
     hipError_t e;
     if ((e = ctx->rec.ensure(items_bytes)) != hipSuccess || (e = ctx->ext.ensure(items_bytes)) != hipSuccess ||
-        (e = ctx->inner.ensure((uint64_t)count * alp::inner_stride(sp.O) * sizeof(uint2))) != hipSuccess ||
-        (e = ctx->done.ensure((uint64_t)count * sizeof(uint32_t))) != hipSuccess ||
-        (e = ctx->winners.ensure(nblocks * sizeof(alp::Winner))) != hipSuccess ||
-        (e = ctx->pruned_counts.ensure(nblocks * sizeof(uint64_t))) != hipSuccess ||
-        (e = ctx->pruned_table.ensure((uint64_t)count * sp.M * sp.Q * F1 * sizeof(uint64_t))) != hipSuccess ||
-        (e = ctx->pruned_orders.ensure((uint64_t)count * alp::pruned_order_bytes())) != hipSuccess)
+        (bpi > 1 &&
+         ((e = ctx->winners.ensure(nblocks * 3 * sizeof(uint64_t))) != hipSuccess ||
+          (e = ctx->fused_words.ensure(alp::block_counter_words(count, bpi) * sizeof(uint32_t))) !=
+              hipSuccess)) ||
+        (e = ctx->pruned_table.ensure(count * alp::pruned_table_entries(sp, F_max, flags) *
+                                      sizeof(uint64_t))) != hipSuccess)
         return hip_fail(e, "hipMalloc(pruned search)");
     if (count > ctx->host_pruned_cap) {
         void *grown = nullptr, *grown_dev = nullptr;
@@ -1549,29 +1547,20 @@ int32_t alp_search_pruned(alp_ctx *ctx, uint32_t count, const uint32_t *instance
     if (st != ALP_OK)
         return st;
     uint2 *rec = (uint2 *)ctx->rec.ptr, *ext = (uint2 *)ctx->ext.ptr;
-    uint32_t *done = (uint32_t *)ctx->done.ptr;
     if (ctx->timing && (e = hipEventRecord(ctx->ev[0], ctx->stream)) != hipSuccess)
         return hip_fail(e, "hipEventRecord");
-    alp::ScanReset reset;
-    reset.done = done;                       // the pruned scan publishes every block's winner
     Marked mark("alp pruned search: option terms, table and scan");
-    if ((e = alp::launch_option_terms(sp, ctx->tdev, q, count, rec, ext, (uint2 *)ctx->inner.ptr,
-                                      reset, ctx->stream)) != hipSuccess)
+    if ((e = alp::launch_option_terms(sp, ctx->tdev, q, count, rec, ext, nullptr,
+                                      alp::ScanReset{}, ctx->stream)) != hipSuccess)
         return hip_fail(e, "option_terms launch");
     if (ctx->timing && (e = hipEventRecord(ctx->ev[1], ctx->stream)) != hipSuccess)
         return hip_fail(e, "hipEventRecord");
-    if ((e = alp::launch_pruned_table(sp, ctx->tdev, q, count, F_max, flags, rec,
-                                      (uint64_t *)ctx->pruned_table.ptr, ctx->pruned_orders.ptr,
-                                      ctx->stream)) != hipSuccess)
-        return hip_fail(e, "pruned table launch");
-    if (ctx->timing && (e = hipEventRecord(ctx->ev[2], ctx->stream)) != hipSuccess)
-        return hip_fail(e, "hipEventRecord");
-    if ((e = alp::launch_pruned_scan(sp, count, F_max, flags,
-                                     (const uint64_t *)ctx->pruned_table.ptr, ctx->pruned_orders.ptr, bpi,
-                                     (alp::Winner *)ctx->winners.ptr,
-                                     (uint64_t *)ctx->pruned_counts.ptr, ext, done,
-                                     ctx->host_pruned_dev, ctx->stream)) != hipSuccess)
-        return hip_fail(e, "pruned scan launch");
+    if ((e = alp::launch_pruned(sp, ctx->tdev, q, count, F_max, flags, rec,
+                                (uint64_t *)ctx->pruned_table.ptr, bpi,
+                                (uint64_t *)ctx->winners.ptr, (uint32_t *)ctx->fused_words.ptr, ext,
+                                ctx->host_pruned_dev, ctx->stream,
+                                ctx->timing ? ctx->ev[2] : nullptr)) != hipSuccess)
+        return hip_fail(e, "pruned search launch");
     if (ctx->timing && (e = hipEventRecord(ctx->ev[3], ctx->stream)) != hipSuccess)
         return hip_fail(e, "hipEventRecord");
     if ((e = hipStreamSynchronize(ctx->stream)) != hipSuccess)
@@ -1816,7 +1805,7 @@ void alp_free(alp_ctx *ctx)
                 (void)hipEventDestroy(x);
     DevBuf *bufs[] = {&ctx->tables, &ctx->q_inst, &ctx->rec, &ctx->ext, &ctx->inner, &ctx->done,
                       &ctx->winners, &ctx->idx, &ctx->evals, &ctx->tmax, &ctx->split_dp,
-                      &ctx->pruned_table, &ctx->pruned_orders, &ctx->pruned_counts,
+                      &ctx->pruned_table,
                       &ctx->place_in, &ctx->place_out, &ctx->pair, &ctx->fused_regions,
                       &ctx->fused_words};
     for (DevBuf *b : bufs)

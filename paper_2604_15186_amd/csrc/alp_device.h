@@ -740,5 +740,29 @@ __device__ __forceinline__ void stage_item_tables(const SpaceDev &sp, const Tabl
     __syncthreads();
 }
 
+// Counts a block of an item as finished, by one lane whose results for the item's last block have
+// been performed (atomics that returned): true for the last of blocks_per_item.  Blocks count in
+// groups of kGroupBlocks, every counter on a line of its own (updates of one line complete 31 ns
+// apart here, and blocks of equal work end together), and the last of a group counts the group.
+// The counters it completed are reset, so they are 0 between launches.
+__device__ __forceinline__ bool count_block(uint32_t *group_done, uint32_t item, uint32_t sub,
+                                            uint32_t blocks_per_item)
+{
+    const uint32_t groups = (blocks_per_item + kGroupBlocks - 1) / kGroupBlocks;
+    const uint32_t g = sub / kGroupBlocks;
+    const uint32_t in_group = g + 1 < groups ? kGroupBlocks : blocks_per_item - g * kGroupBlocks;
+    uint32_t *line = group_done + (uint64_t)item * (groups + 1) * kCounterLine;
+    uint32_t *gd = line + (1 + g) * kCounterLine;
+    if (atomicAdd(gd, 1u) != in_group - 1)
+        return false;
+    (void)atomicExch(gd, 0u);
+    if (groups == 1)
+        return true;
+    if (atomicAdd(line, 1u) != groups - 1)
+        return false;
+    (void)atomicExch(line, 0u);
+    return true;
+}
+
 }  // namespace
 }  // namespace alp

@@ -165,9 +165,13 @@ struct FusedArgs {
     unsigned long long *best;
     unsigned long long *slots; // packed scan: per block, its lowest (latency, lanes' index)
 };
-// Packed scan: blocks counted together, and the distance of its counters in 32-bit words (an item
-// has one for its groups, then one per group, in group_done).
-constexpr uint32_t kPackedGroup = 16, kPackedLine = 32;
+// count_block(): blocks counted together, and the distance of its counters in 32-bit words (an
+// item has one for its groups, then one per group).
+constexpr uint32_t kGroupBlocks = 16, kCounterLine = 32;
+__host__ __device__ inline uint64_t block_counter_words(uint64_t items, uint32_t blocks_per_item)
+{
+    return items * (1 + (blocks_per_item + kGroupBlocks - 1) / kGroupBlocks) * kCounterLine;
+}
 // Blocks of an item counted together before the item's count (two-level counting, so that at
 // most this many blocks update one counter word).
 constexpr uint32_t kFusedGroup = 64;
@@ -260,21 +264,17 @@ hipError_t launch_tmax(const SpaceDev &sp, const QueryDev &q, uint32_t count, co
 hipError_t launch_allocate(const alp_result_t *res, uint32_t W, uint32_t G, uint32_t policy,
                            uint64_t *dp, alp_plan_t *plan, uint32_t *gpus, hipStream_t st);
 
-// The paper's pruned search for count items (see alp_search_pruned), after the option-term
-// kernel (rec, ext; it also zeroes done[]).  launch_pruned_table fills `table`
-// (count * M * Q * (F_max + 1) entries) and `orders` (count records of pruned_order_bytes());
-// launch_pruned_scan runs blocks_per_item blocks of 256 threads per item, covering
-// pruned_prefixes(M, F_max) threads; winners and counts hold count * blocks_per_item entries.
-// Writes out[0..count).
-uint64_t pruned_prefixes(uint32_t M, uint32_t F_max);
-size_t pruned_order_bytes();
-hipError_t launch_pruned_table(const SpaceDev &sp, const TablesDev &tb, const QueryDev &q,
-                               uint32_t count, uint32_t F_max, uint32_t flags, const uint2 *rec,
-                               uint64_t *table, void *orders, hipStream_t st);
-hipError_t launch_pruned_scan(const SpaceDev &sp, uint32_t count, uint32_t F_max, uint32_t flags,
-                              const uint64_t *table, const void *orders, uint32_t blocks_per_item,
-                              Winner *winners, uint64_t *counts, const uint2 *ext, uint32_t *done,
-                              alp_pruned_t *out, hipStream_t st);
+// The paper's pruned search for count items of at most F_max units (see alp_search_pruned), after
+// the option-term kernel (rec, ext).  table: count * pruned_table_entries() entries of device
+// memory (0: the blocks build it in LDS); pruned_blocks_per_item() blocks per item, three words of
+// slots for each, and block_counter_words() counters, 0 between launches.  Records table_done (if given) before the enumeration.  Writes out[0..count).
+uint64_t pruned_table_entries(const SpaceDev &sp, uint32_t F_max, uint32_t flags);
+uint32_t pruned_blocks_per_item(uint32_t M, uint32_t F_max, uint32_t count);
+hipError_t launch_pruned(const SpaceDev &sp, const TablesDev &tb, const QueryDev &q, uint32_t count,
+                         uint32_t F_max, uint32_t flags, const uint2 *rec, uint64_t *table,
+                         uint32_t blocks_per_item, uint64_t *slots, uint32_t *counters,
+                         const uint2 *ext, alp_pruned_t *out, hipStream_t st,
+                         hipEvent_t table_done);
 
 static_assert(sizeof(alp_stats_t) == 32 && offsetof(alp_stats_t, calls) == 8 &&
                   offsetof(alp_stats_t, active_us) == 24,

@@ -480,12 +480,9 @@ scan_packed_kernel(QueryDev q, PackedPlan pk, uint32_t blocks_per_item, uint32_t
     if (blocks_per_item > 1) {
         // Equal tiles end together, so nothing may queue behind the item's other blocks: each
         // block puts its winner in its own slot (one word, (L, X), unless X needs more; atomic
-        // exchanges, performed at the agent's point of coherence once they return), then counts
-        // itself in its group of kPackedGroup blocks, groups 128 bytes apart, and the last of a
-        // group counts the group.  The item's last block resets the counters it completed and
-        // reads every slot, by atomics too.  (One word raised by atomic maxima, with groups of 64
-        // in one line, cost the 4-LLM search of 256 blocks 8 us: such updates complete 31 ns
-        // apart.)
+        // exchanges, performed at the agent's point of coherence once they return) and counts
+        // itself; the item's last block reads every slot, by atomics too.  (One word raised by
+        // atomic maxima, with groups of 64 in one line, cost the 4-LLM search of 256 blocks 8 us.)
         unsigned long long *slots =
             fz.slots + (uint64_t)item * blocks_per_item * (pk.wide_index ? 2 : 1);
         uint32_t last = 0;
@@ -497,21 +494,7 @@ scan_packed_kernel(QueryDev q, PackedPlan pk, uint32_t blocks_per_item, uint32_t
                 (void)atomicExch(slots + sub, ((unsigned long long)L << 32) | (uint32_t)X);
             }
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            const uint32_t groups = (blocks_per_item + kPackedGroup - 1) / kPackedGroup;
-            const uint32_t g = sub / kPackedGroup;
-            const uint32_t in_group =
-                g + 1 < groups ? kPackedGroup : blocks_per_item - g * kPackedGroup;
-            uint32_t *line = fz.group_done + (uint64_t)item * (groups + 1) * kPackedLine;
-            uint32_t *gd = line + (1 + g) * kPackedLine;
-            if (atomicAdd(gd, 1u) == in_group - 1) {
-                (void)atomicExch(gd, 0u);              // 0 between launches
-                if (groups == 1) {
-                    last = 1;
-                } else if (atomicAdd(line, 1u) == groups - 1) {
-                    (void)atomicExch(line, 0u);
-                    last = 1;
-                }
-            }
+            last = count_block(fz.group_done, item, sub, blocks_per_item) ? 1u : 0u;
         }
         if (!__builtin_amdgcn_readfirstlane((int)last))
             return;

@@ -1,0 +1,63 @@
+"""The pruned search's enumeration against the oracle at the edges of its tables and prefixes, on an
+MI355X: option tables at and beyond what a block holds in LDS (with and without the ordering), one
+share unit per GPU, one to eight LLMs, several blocks per item and many items in a batch."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+from workloads import make_custom, target_from_tmax
+
+pytestmark = pytest.mark.gpu
+
+# seed, M, share units per GPU, budgets, flags
+POINTS = [
+    (301, 1, 4, (0, 3, 16), (0, 3)),
+    (302, 2, 16, (128, 127, 1), (0, 1, 2, 3)),        # 2,048 units (the most): table in memory
+    (303, 3, 8, (120, 7), (0, 3)),                    # 960 units: in memory
+    (304, 3, 10, (82, 81), (1, 3)),                   # 820 units: the most a block holds in LDS
+    (310, 3, 10, (83, 82), (1, 3)),                   # beyond
+    (305, 4, 1, (40, 13, 3, 4), (0, 1, 2, 3)),        # one unit per GPU
+    (306, 4, 16, (10, 1), (2, 3)),
+    (307, 5, 3, (11, 5), (0, 1, 2, 3)),
+    (308, 7, 2, (9, 3), (0, 3)),
+    (309, 8, 2, (8,), (1, 3)),
+]
+
+
+@pytest.fixture(scope="module")
+def alp():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2604_15186_amd import alp as binding
+    binding.lib()
+    return binding
+
+
+@pytest.mark.parametrize("point", POINTS, ids=[f"seed{p[0]}" for p in POINTS])
+def test_matches_the_oracle(alp, point):
+    seed, M, Q, budgets, flag_sets = point
+    fq = sorted({max(1, round(Q * k / 4)) for k in range(1, 5)})
+    b = make_custom(seed, M, (1, 2, 4, 8), fq, 8, 4, max(budgets), count=2, frac_den=Q, alpha=0.7)
+    inst = np.asarray([0, 1] * len(budgets), np.uint32)
+    G = np.repeat(np.asarray(budgets, np.uint32), 2)
+    objs = [oracle.Instance(b, 0), oracle.Instance(b, 1)]
+    lam = [max(1, target_from_tmax(300_000, oracle.tmax(objs[i], int(g))) // (1 + k % 3))
+           for k, (i, g) in enumerate(zip(inst, G))]
+    with alp.Context(b) as ctx:
+        for flags in flag_sets:
+            want = [oracle.pruned(objs[i], int(g), int(v), flags) for i, g, v in zip(inst, G, lam)]
+            for reps in (1, 40):                      # several blocks per item, then many items
+                out = ctx.search_pruned(np.tile(G, reps), np.tile(lam, reps), flags,
+                                        instances=np.tile(inst, reps))
+                for k, r in enumerate(out):
+                    w = want[k % len(want)]
+                    got = (int(r["vectors"]), int(r["unpruned"]))
+                    assert got == (w["vectors"], w["unpruned"]), (flags, k)
+                    if w["x"] is None:
+                        assert int(r["best"]["status"]) == alp.ALP_INFEASIBLE
+                    else:
+                        assert (int(r["best"]["index"]), int(r["best"]["latency_us"])) == \
+                            (w["x"], w["L"]), (flags, k)

@@ -303,7 +303,7 @@ int32_t alp_stats_create(alp_stats_ctx **out, int32_t device, void *hip_stream);
  * more.  Synchronous on the context's stream.  Any call order within a trace gives the same
  * result; traces whose calls are in order of end time (as logged on completion) and that span
  * under 2^32 us take the fast path (no sort).  A context whose call finds most traces out of
- * end order sorts every trace directly on its next 7 calls, then checks the order again.  The
+ * end order sorts every trace directly from its next call on, until it finds most in order.  The
  * context's scratch grows to 4 bytes per trace plus, for traces beyond 2,048 calls, 16 bytes
  * per call rounded up to a power of two per trace. */
 int32_t alp_trace_stats(alp_stats_ctx *ctx, uint32_t num_llms, uint32_t num_traces,

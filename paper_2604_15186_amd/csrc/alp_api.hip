@@ -952,12 +952,28 @@ int32_t launch_search(alp_ctx *c, const alp::QueryDev &q, uint32_t count, alp_re
     return launch_search_with(c, q, count, out, raw, ev, g, s, signal, seq);
 }
 
+// Waits for a kernel's last block to store seq in a mapped host word, rather than for the kernel's
+// completion to reach the host.  After the first millisecond the wait also polls the stream, once
+// a millisecond (a poll costs microseconds, so it stays off the path of short work); false when
+// the stream has ended (or failed) without the signal: the caller synchronises, which reports any
+// error.
+bool wait_signal(const uint32_t *word, uint32_t seq, hipStream_t stream)
+{
+    auto poll_at = std::chrono::steady_clock::now() + std::chrono::milliseconds(1);
+    for (uint32_t k = 1;; ++k) {
+        if (__atomic_load_n(word, __ATOMIC_ACQUIRE) == seq)
+            return true;
+        if ((k & 255) == 0 && std::chrono::steady_clock::now() >= poll_at) {
+            if (hipStreamQuery(stream) != hipErrorNotReady)
+                return false;
+            poll_at = std::chrono::steady_clock::now() + std::chrono::milliseconds(1);
+        }
+        __builtin_ia32_pause();
+    }
+}
+
 // Synchronous searches: results in the context's mapped host buffer.  A single untimed search
-// has its record signalled in host memory (FinishArgs::signal): the caller reads it as soon as
-// the kernel's last block has written it, rather than after the kernel's completion reaches
-// the host.  After the first millisecond the wait also polls the stream, once a millisecond
-// (a poll costs microseconds, so it stays off the path of short searches); a stream that ends
-// (or fails) without the signal falls back to the synchronisation, which reports any error.
+// has its record signalled in host memory (FinishArgs::signal).
 int32_t run_search(alp_ctx *c, const alp::QueryDev &q, uint32_t count)
 {
     int32_t st = ensure_host_results(c, count);
@@ -973,20 +989,7 @@ int32_t run_search(alp_ctx *c, const alp::QueryDev &q, uint32_t count)
                             signalled ? c->host_signal_dev : nullptr, seq)) != ALP_OK)
         return st;
     hipError_t e = hipSuccess;
-    bool seen = false;
-    auto poll_at = std::chrono::steady_clock::now() + std::chrono::milliseconds(1);
-    for (uint32_t k = 1; signalled; ++k) {
-        if (__atomic_load_n(c->host_signal, __ATOMIC_ACQUIRE) == seq) {
-            seen = true;
-            break;
-        }
-        if ((k & 255) == 0 && std::chrono::steady_clock::now() >= poll_at) {
-            if (hipStreamQuery(c->stream) != hipErrorNotReady)
-                break;
-            poll_at = std::chrono::steady_clock::now() + std::chrono::milliseconds(1);
-        }
-        __builtin_ia32_pause();
-    }
+    const bool seen = signalled && wait_signal(c->host_signal, seq, c->stream);
     if (!seen && (e = hipStreamSynchronize(c->stream)) != hipSuccess)
         return hip_fail(e, "hipStreamSynchronize");
     if (c->timing) {
@@ -1837,13 +1840,15 @@ struct alp_stats_ctx {
     int timing = 0;
     hipEvent_t ev[2] = {nullptr, nullptr};
     float last_ms = 0.0f;
-    // Calls left that sort every trace without the end-order sweep: set when a sweep found most
-    // traces out of end order (each such trace is then loaded twice), counted down per call, so
-    // that every kStatsProbeEvery-th call measures the order again.
-    uint32_t direct_left = 0;
+    // How the next call starts, from what the last one saw: sorting every trace without the
+    // end-order sweep (a sweep found most traces out of end order, each of which is then loaded
+    // twice; the direct sort counts the traces in end order and goes back once most are), with
+    // groups for traces of up to direct_max calls; and reading the offsets first (there were
+    // traces beyond kStatsShortMax calls, which need scratch and a pass of their own).
+    bool direct = false, plan_first = false;
+    uint32_t direct_max = 0;
+    uint32_t seq = 0;
 };
-
-constexpr uint32_t kStatsProbeEvery = 8;
 
 int32_t alp_stats_create(alp_stats_ctx **out, int32_t device, void *hip_stream)
 {
@@ -1862,6 +1867,8 @@ int32_t alp_stats_create(alp_stats_ctx **out, int32_t device, void *hip_stream)
                          hipHostMallocMapped);
     if (e == hipSuccess)
         e = hipHostGetDevicePointer((void **)&c->host_out_dev, c->host_out, 0);
+    if (e == hipSuccess)
+        memset(c->host_out, 0, (ALP_MAX_LLMS + 1) * sizeof(alp_stats_t));
     for (int k = 0; k < 2 && e == hipSuccess; ++k)
         e = hipEventCreate(&c->ev[k]);
     if (e == hipSuccess)
@@ -1874,22 +1881,39 @@ int32_t alp_stats_create(alp_stats_ctx **out, int32_t device, void *hip_stream)
     return ALP_OK;
 }
 
-int32_t alp_trace_stats(alp_stats_ctx *c, uint32_t num_llms, uint32_t num_traces,
-                        const uint64_t *offsets, const uint32_t *llm, const uint64_t *start_us,
-                        const uint64_t *end_us, alp_stats_t *out)
+namespace {
+
+// One launch sequence of the statistics and the wait for its last block's StatsTail.
+int32_t stats_launch(alp_stats_ctx *c, alp::StatsLaunch &l, alp::StatsTail &tail)
 {
-    constexpr uint64_t kMaxTrace = 1ull << 24, kLdsMax = 2048;   // 2 x 2048 x 8 B of LDS
-    if (!c || !offsets || !out)
-        return fail(ALP_EINVAL, "ctx, offsets or out is NULL");
-    if (num_llms < 1 || num_llms > ALP_MAX_LLMS)
-        return fail(ALP_EINVAL, "num_llms %u outside 1..%d", num_llms, ALP_MAX_LLMS);
-    if (num_traces < 1 || num_traces >= (1u << 31))
-        return fail(ALP_EINVAL, "num_traces %u outside 1..2^31-1", num_traces);
-    DeviceGuard guard(c->device);
-    if (guard.status != hipSuccess)
-        return hip_fail(guard.status, "hipSetDevice");
     hipError_t e;
-    const size_t n_off = (size_t)num_traces + 1;
+    l.zero_first = !c->counters_clean;
+    c->counters_clean = false;                         // until the kernels have run to the end
+    if (++c->seq == 0)
+        ++c->seq;                                      // 0 is the word's initial value
+    l.seq = c->seq;
+    alp::StatsTail *host = (alp::StatsTail *)(c->host_out + ALP_MAX_LLMS);
+    Marked mark("alp trace statistics");
+    if ((e = alp::launch_trace_stats(l, c->stream)) != hipSuccess)
+        return hip_fail(e, "statistics launch");
+    if (!wait_signal(&host->seq, l.seq, c->stream)) {
+        if ((e = hipStreamSynchronize(c->stream)) != hipSuccess)
+            return hip_fail(e, "statistics");
+        if (__atomic_load_n(&host->seq, __ATOMIC_ACQUIRE) != l.seq)
+            return fail(ALP_EDEVICE, "statistics: the kernels ended without a result");
+    }
+    c->counters_clean = true;
+    memcpy(&tail, host, sizeof(tail));
+    return ALP_OK;
+}
+
+// Reads the offsets, checks them, and lists the traces beyond kStatsShortMax calls with their
+// scratch; max_short: the most calls of the others.
+int32_t stats_plan(alp_stats_ctx *c, alp::StatsLaunch &l, uint64_t &max_short)
+{
+    constexpr uint64_t kMaxTrace = 1ull << 24;
+    hipError_t e;
+    const size_t n_off = (size_t)l.R + 1;
     if (c->offsets_cap < n_off) {
         // Pinned, so the copy goes straight to it (no staging through a bounce buffer).
         void *grown = nullptr;
@@ -1901,7 +1925,7 @@ int32_t alp_trace_stats(alp_stats_ctx *c, uint32_t num_llms, uint32_t num_traces
         c->offsets = (uint64_t *)grown;
         c->offsets_cap = n_off;
     }
-    if ((e = hipMemcpyAsync(c->offsets, offsets, n_off * sizeof(uint64_t),
+    if ((e = hipMemcpyAsync(c->offsets, l.offsets, n_off * sizeof(uint64_t),
                             hipMemcpyDeviceToHost, c->stream)) != hipSuccess ||
         (e = hipStreamSynchronize(c->stream)) != hipSuccess)
         return hip_fail(e, "copy offsets");
@@ -1909,14 +1933,14 @@ int32_t alp_trace_stats(alp_stats_ctx *c, uint32_t num_llms, uint32_t num_traces
         return fail(ALP_EINVAL, "offsets[0] = %llu, not 0", (unsigned long long)c->offsets[0]);
     std::vector<uint32_t> longs;
     std::vector<uint64_t> bases;
-    uint64_t max_short = 0, scratch_pairs = 0;
-    for (uint32_t r = 0; r < num_traces; ++r) {
+    uint64_t scratch_pairs = 0;
+    for (uint32_t r = 0; r < l.R; ++r) {
         if (c->offsets[r + 1] < c->offsets[r])
             return fail(ALP_EINVAL, "offsets decrease at trace %u", r);
         const uint64_t n = c->offsets[r + 1] - c->offsets[r];
         if (n > kMaxTrace)
             return fail(ALP_ERANGE, "trace %u has %llu calls (at most 2^24)", r, (unsigned long long)n);
-        if (n > kLdsMax) {
+        if (n > alp::kStatsShortMax) {
             uint64_t P = 256;
             while (P < n)
                 P <<= 1;
@@ -1927,11 +1951,8 @@ int32_t alp_trace_stats(alp_stats_ctx *c, uint32_t num_llms, uint32_t num_traces
             max_short = n;
         }
     }
-    if (c->offsets[num_traces] > 0 && (!llm || !start_us || !end_us))
+    if (c->offsets[l.R] > 0 && (!l.llm || !l.start || !l.end))
         return fail(ALP_EINVAL, "llm, start_us or end_us is NULL");
-    uint32_t lds_cap = 256;
-    while (lds_cap < max_short)
-        lds_cap <<= 1;
     if (!longs.empty()) {
         if ((e = c->long_list.ensure(longs.size() * sizeof(uint32_t))) != hipSuccess ||
             (e = c->long_base.ensure(bases.size() * sizeof(uint64_t))) != hipSuccess ||
@@ -1940,47 +1961,113 @@ int32_t alp_trace_stats(alp_stats_ctx *c, uint32_t num_llms, uint32_t num_traces
         if ((e = hipMemcpyAsync(c->long_list.ptr, longs.data(), longs.size() * sizeof(uint32_t),
                                 hipMemcpyHostToDevice, c->stream)) != hipSuccess ||
             (e = hipMemcpyAsync(c->long_base.ptr, bases.data(), bases.size() * sizeof(uint64_t),
-                                hipMemcpyHostToDevice, c->stream)) != hipSuccess)
+                                hipMemcpyHostToDevice, c->stream)) != hipSuccess ||
+            (e = hipStreamSynchronize(c->stream)) != hipSuccess)     // the vectors go away
             return hip_fail(e, "copy long traces");
     }
+    l.num_long = (uint32_t)longs.size();
+    l.long_traces = (const uint32_t *)c->long_list.ptr;
+    l.long_base = (const uint64_t *)c->long_base.ptr;
+    l.scratch = (uint64_t *)c->scratch.ptr;
+    return ALP_OK;
+}
+
+}  // namespace
+
+int32_t alp_trace_stats(alp_stats_ctx *c, uint32_t num_llms, uint32_t num_traces,
+                        const uint64_t *offsets, const uint32_t *llm, const uint64_t *start_us,
+                        const uint64_t *end_us, alp_stats_t *out)
+{
+    if (!c || !offsets || !out)
+        return fail(ALP_EINVAL, "ctx, offsets or out is NULL");
+    if (num_llms < 1 || num_llms > ALP_MAX_LLMS)
+        return fail(ALP_EINVAL, "num_llms %u outside 1..%d", num_llms, ALP_MAX_LLMS);
+    if (num_traces < 1 || num_traces >= (1u << 31))
+        return fail(ALP_EINVAL, "num_traces %u outside 1..2^31-1", num_traces);
+    DeviceGuard guard(c->device);
+    if (guard.status != hipSuccess)
+        return hip_fail(guard.status, "hipSetDevice");
+    hipError_t e;
     if ((e = c->work.ensure((uint64_t)num_traces * sizeof(uint32_t))) != hipSuccess)
         return hip_fail(e, "hipMalloc(statistics work list)");
-    uint64_t *totals = (uint64_t *)c->totals.ptr;
-    const bool sweep = c->direct_left == 0;
-    if (!sweep)
-        --c->direct_left;
+    alp::StatsLaunch l{};
+    l.M = num_llms;
+    l.R = num_traces;
+    l.offsets = offsets;
+    l.llm = llm;
+    l.start = start_us;
+    l.end = end_us;
+    l.totals = (uint64_t *)c->totals.ptr;
+    l.work = (uint32_t *)c->work.ptr;
+    l.out = c->host_out_dev;
+    l.order = c->direct ? alp::kStatsDirect : alp::kStatsSweep;
+    l.lds_cap = alp::kStatsShortMax;
+    l.max_short = c->direct_max;
     if (c->timing && (e = hipEventRecord(c->ev[0], c->stream)) != hipSuccess)
         return hip_fail(e, "hipEventRecord");
-    const bool zero_first = !c->counters_clean;
-    c->counters_clean = false;                       // until the kernels have run to the end
-    Marked mark("alp trace statistics");
-    if ((e = alp::launch_trace_stats(num_llms, num_traces, offsets, llm, start_us, end_us, lds_cap,
-                                     (uint32_t)max_short, (uint32_t)longs.size(), (const uint32_t *)c->long_list.ptr,
-                                     (const uint64_t *)c->long_base.ptr, (uint64_t *)c->scratch.ptr,
-                                     totals, (uint32_t *)c->work.ptr, sweep, zero_first,
-                                     c->host_out_dev, c->stream)) != hipSuccess)
-        return hip_fail(e, "statistics launch");
-    if (c->timing && (e = hipEventRecord(c->ev[1], c->stream)) != hipSuccess)
-        return hip_fail(e, "hipEventRecord");
-    if ((e = hipStreamSynchronize(c->stream)) != hipSuccess)
-        return hip_fail(e, "statistics");
-    c->counters_clean = true;
-    // The status and the work list's length, written by the last block after the records.
     alp::StatsTail tail;
-    memcpy(&tail, c->host_out + ALP_MAX_LLMS, sizeof(tail));
-    const uint32_t host_flags = tail.flags;
-    const uint64_t short_traces = num_traces - longs.size();
-    if (sweep && 2 * (uint64_t)tail.listed > short_traces)
-        c->direct_left = kStatsProbeEvery - 1;
-    if (c->timing && (e = hipEventElapsedTime(&c->last_ms, c->ev[0], c->ev[1])) != hipSuccess)
-        return hip_fail(e, "hipEventElapsedTime");
-    if (host_flags & 1u)
+    uint64_t long_traces = 0;
+    int32_t st = ALP_OK;
+    // Without the offsets on the host where the call can do without: one launch sequence and one
+    // wait.  The kernels check the offsets; bad ones are read here for the error, and traces
+    // beyond the short ones' length take a second launch.
+    bool plan = c->plan_first || !llm || !start_us || !end_us;
+    if (!plan) {
+        if ((st = stats_launch(c, l, tail)) != ALP_OK)
+            return st;
+        long_traces = tail.longs;
+        if (tail.flags & 16u) {
+            c->counters_clean = false;
+            plan = true;
+        }
+    }
+    if (plan || long_traces) {
+        uint64_t max_short = 0;
+        if ((st = stats_plan(c, l, max_short)) != ALP_OK) {
+            c->counters_clean = false;
+            return st;
+        }
+        long_traces = l.num_long;
+        l.planned = true;
+        if (plan) {
+            l.lds_cap = 256;
+            while (l.lds_cap < max_short)
+                l.lds_cap <<= 1;
+            l.max_short = (uint32_t)max_short;
+        } else {
+            l.order = alp::kStatsLongOnly;
+        }
+        const alp::StatsTail first = tail;
+        if ((st = stats_launch(c, l, tail)) != ALP_OK)
+            return st;
+        if (!plan) {                                   // what the first launch saw
+            tail.listed = first.listed;
+            tail.longest = first.longest;
+            tail.in_order = first.in_order;
+        }
+    }
+    c->plan_first = long_traces != 0;
+    const uint64_t short_traces = num_traces - long_traces;
+    if (!c->direct) {
+        c->direct = 2 * (uint64_t)tail.listed > short_traces;
+        c->direct_max = alp::kStatsShortMax;
+    } else {
+        c->direct = 2 * (uint64_t)tail.in_order <= short_traces;
+        c->direct_max = tail.longest;
+    }
+    if (c->timing) {
+        if ((e = hipEventRecord(c->ev[1], c->stream)) != hipSuccess ||
+            (e = hipEventSynchronize(c->ev[1])) != hipSuccess ||
+            (e = hipEventElapsedTime(&c->last_ms, c->ev[0], c->ev[1])) != hipSuccess)
+            return hip_fail(e, "statistics time");
+    }
+    if (tail.flags & 1u)
         return fail(ALP_EINVAL, "a call's llm index is not below num_llms");
-    if (host_flags & 2u)
+    if (tail.flags & 2u)
         return fail(ALP_EINVAL, "a call ends before it starts");
-    if (host_flags & 4u)
+    if (tail.flags & 4u)
         return fail(ALP_ERANGE, "a start time of 2^60 us or more, or a duration of 2^32 us or more");
-    if (host_flags & 8u)
+    if (tail.flags & 8u)
         return fail(ALP_ERANGE, "n or p of 2^31 thousandths or more");
     memcpy(out, c->host_out, num_llms * sizeof(alp_stats_t));
     return ALP_OK;

@@ -283,35 +283,55 @@ static_assert(sizeof(alp_pruned_t) == 64 && offsetof(alp_pruned_t, fraction_vect
                   offsetof(alp_pruned_t, unpruned_vectors) == 56,
               "alp_pruned_t layout");
 
-// Workflow statistics (see alp_trace_stats).  Traces up to lds_cap calls (a power of two,
-// 256..2048) are swept or sorted in LDS; the num_long others (long_traces[]) are sorted in
-// scratch, trace k at 2 * long_base[k] words (2 * pow2(length) words each).  totals:
-// kStatsTotalsWords + kStatsTailWords words: kStatsCopies copies of the per-LLM sums,
-// kStatsCopyStride words apart (trace r adds to copy r mod kStatsCopies, so that thousands of
-// traces do not queue on the same atomic words), then the status flags (one word), the length
-// of the work list and the count of finished slots (the low and high half of the next), and
-// kStatsSlots 32-bit counters of finished blocks.  They must be zero when the kernels start; the last block leaves them zero,
-// so zero_first is needed only for fresh memory or after a failed launch.  sweep: traces in end order are swept without a sort and the others listed in work
-// (R entries) for the sort pass; otherwise every trace is sorted.  max_short: the most calls of
-// a trace within lds_cap (direct sorts launch only the group sizes it reaches).  Writes
-// out[0..M) and the StatsTail at out[ALP_MAX_LLMS].
+// Workflow statistics (see alp_trace_stats).  totals: kStatsTotalsWords + kStatsTailWords words:
+// kStatsCopies copies of the per-LLM sums (and the direct sort's measures), kStatsCopyStride words
+// apart (trace r adds to copy r mod kStatsCopies, so that thousands of traces do not queue on the
+// same atomic words), then the status flags and the count of long traces (the low and high half of
+// one word), the length of the work list and the count of finished slots (of the next), and
+// kStatsSlots 32-bit counters of finished blocks.  They must be zero when the kernels start; the
+// last block leaves them zero, so zero_first is needed only for fresh memory or after a failed
+// launch.
 constexpr uint32_t kStatsCopies = 64;
-constexpr uint32_t kStatsCopyStride = 32;                 // >= 3 * ALP_MAX_LLMS, 256 B apart
+constexpr uint32_t kStatsCopyStride = 32;                 // >= 3 * ALP_MAX_LLMS + 2, 256 B apart
 constexpr uint32_t kStatsTotalsWords = kStatsCopies * kStatsCopyStride;
 constexpr uint32_t kStatsSlots = 64;
 constexpr uint32_t kStatsTailWords = 2 + kStatsSlots / 2;
+constexpr uint32_t kStatsShortMax = 2048;                 // calls of a trace swept or sorted in LDS
 struct StatsTail {
     uint32_t flags;                   // status bits (see alp_trace_stats)
     uint32_t listed;                  // traces the sweep left to the sort pass
-    uint32_t pad[6];
+    uint32_t longs;                   // traces beyond kStatsShortMax, left to a second launch
+    uint32_t longest, in_order;       // direct sort: longest trace above 512 calls (0: none), and
+                                      // traces whose calls came in end order
+    uint32_t pad[2];
+    uint32_t seq;                     // the launch's seq, stored last
 };
 static_assert(sizeof(StatsTail) == sizeof(alp_stats_t), "the tail takes one record's place");
-hipError_t launch_trace_stats(uint32_t M, uint32_t R, const uint64_t *offsets, const uint32_t *llm,
-                              const uint64_t *start, const uint64_t *end, uint32_t lds_cap,
-                              uint32_t max_short, uint32_t num_long, const uint32_t *long_traces,
-                              const uint64_t *long_base, uint64_t *scratch, uint64_t *totals,
-                              uint32_t *work, bool sweep, bool zero_first, alp_stats_t *out,
-                              hipStream_t st);
+// What a launch does with the traces of at most lds_cap calls: sweeps those in end order and lists
+// the others in work (R entries) for the sort pass; sorts every one directly (group sizes up to
+// max_short calls; longer ones are listed); or leaves them (an earlier launch summed them, and only
+// the long traces are to come).
+enum StatsOrder { kStatsSweep, kStatsDirect, kStatsLongOnly };
+struct StatsLaunch {
+    StatsOrder order;
+    uint32_t M, R;
+    const uint64_t *offsets;
+    const uint32_t *llm;
+    const uint64_t *start, *end;
+    uint32_t lds_cap;                 // a power of two, 256..kStatsShortMax
+    uint32_t max_short;
+    bool planned;                     // the host has read the offsets; otherwise the kernels check
+                                      // them and count the long traces
+    uint32_t num_long;                // planned: traces beyond lds_cap, long_traces[], sorted in
+    const uint32_t *long_traces;      // scratch, trace k at 2 * long_base[k] words
+    const uint64_t *long_base;        // (2 * pow2(length) words each)
+    uint64_t *scratch, *totals;
+    uint32_t *work;
+    bool zero_first;
+    alp_stats_t *out;                 // M records, then the StatsTail at out[ALP_MAX_LLMS]
+    uint32_t seq;
+};
+hipError_t launch_trace_stats(const StatsLaunch &l, hipStream_t st);
 
 // One allocation to place: budget, LLM count, whether the search found it, per-LLM choices,
 // and the index of its output record.

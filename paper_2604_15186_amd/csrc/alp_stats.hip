@@ -324,9 +324,51 @@ struct StatsArgs {
     uint32_t *work_count;
     uint32_t *done;                   // participants of the sort and long passes done
     uint32_t *slot_done;              // kStatsSlots counters of those participants
-    uint32_t sort_grid, num_long;     // blocks of the sort and long launches
+    uint32_t sort_grid, num_long;     // blocks of the sort and long launches (0: none)
     alp_stats_t *out;                 // M records, then the StatsTail
+    // planned: the host has read the offsets (they ascend; long_traces are the traces beyond
+    // lds_cap).  Otherwise every pass checks a trace's offsets before it reads a call, and the
+    // pass that sees every trace reports bad offsets (flag 16) and counts the long traces; with
+    // any, the last block leaves the totals to a second launch of the long pass.
+    uint32_t planned;
+    uint32_t *long_count;
+    uint32_t group_max;               // direct sort: the longest trace the group launches take
+    uint32_t seq;                     // stored in the StatsTail last, with a release
 };
+
+// Words of a copy of the totals after the sums: the longest trace and the traces in end order, as
+// the direct sort sees them.
+constexpr uint32_t kLongestWord = 3 * ALP_MAX_LLMS, kInOrderWord = kLongestWord + 1;
+static_assert(kInOrderWord < kStatsCopyStride, "a copy holds its measures");
+
+// Trace r's calls, [lo, lo + n); false (n = 0) if its offsets are bad.  The call arrays hold
+// offsets[R] entries, so a trace within them is safe to read whatever the other offsets are.
+__device__ __forceinline__ bool trace_calls(const StatsArgs &a, uint32_t r, uint64_t &lo,
+                                            uint64_t &n)
+{
+    lo = a.offsets[r];
+    const uint64_t hi = a.offsets[r + 1];
+    n = hi - lo;
+    if (a.planned)
+        return true;
+    const bool ok = hi >= lo && hi <= a.offsets[a.R] && n <= (1ull << 24) && (r != 0 || lo == 0);
+    n = ok ? n : 0;
+    return ok;
+}
+
+// The same for the pass that sees every trace, by one lane's reports: true if the trace is short.
+__device__ __forceinline__ bool short_trace(const StatsArgs &a, uint32_t r, uint32_t lane,
+                                            uint64_t &lo, uint64_t &n)
+{
+    const bool ok = trace_calls(a, r, lo, n);
+    if (!a.planned && lane == 0) {
+        if (!ok)
+            atomicOr(a.flags, 16u);
+        else if (n > a.lds_cap)
+            atomicAdd(a.long_count, 1u);
+    }
+    return n != 0 && n <= a.lds_cap;
+}
 
 // Wave-wide sum of 32-bit values (every lane gets it).
 __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v)
@@ -528,14 +570,15 @@ __device__ __forceinline__ void group_sweep_regs(const uint64_t (&k)[E], uint32_
 // Keys of the calls lo .. lo + n - 1 (n <= NT E) for thread t of a group of NT: calls j NT + t
 // (j < E; each load instruction reads consecutive calls), keyed by start relative to base.
 // Malformed calls are reported in bad and left out, as in the block sort; a valid call outside
-// [base, base + 2^29) sets far (the group then hands the trace to the block sort).  Loads go
+// [base, base + 2^29) sets far (the group then hands the trace to the block sort); falls: a call
+// ends before the one before it (low words compared: only a measure of the traces' order).  Loads go
 // in groups of up to 4 keys, all in flight together and without branches: positions past the
 // trace load its last call again and become padding.  (A branch per call made the compiler
 // wait for each call's loads before the next; all E at once spill.)
 template <int E, int NT>
 __device__ __forceinline__ void load_keys(const StatsArgs &a, uint64_t lo, uint32_t n, uint32_t t,
                                           uint64_t base, uint64_t (&k)[E], uint32_t &bad,
-                                          uint32_t &valid, bool &far)
+                                          uint32_t &valid, bool &far, bool &falls)
 {
     const uint32_t M = a.M;
     constexpr int kGroup = E < 4 ? E : 4;
@@ -556,6 +599,9 @@ __device__ __forceinline__ void load_keys(const StatsArgs &a, uint64_t lo, uint3
             const uint32_t i = (uint32_t)(j0 + g) * NT + t;
             const uint32_t m = mm[g];
             const uint64_t st = ss[g], en = ee[g];
+            // In end order as far as a wave's own calls tell (its first has no neighbour here).
+            const uint32_t en_lo = (uint32_t)en, before = dpp_mov<0x138>(en_lo, en_lo);
+            falls = falls || (i < n && (int32_t)(en_lo - before) < 0);
             const uint32_t b = m >= M ? 1u
                              : en < st ? 2u
                              : st >= kStartLimit || en - st >= kDurationLimit ? 4u : 0u;
@@ -584,7 +630,8 @@ __device__ __forceinline__ void one_trace(const StatsArgs &a, uint32_t r, uint32
     uint32_t *flags = a.flags;
     __shared__ unsigned long long s_sum[3 * ALP_MAX_LLMS];   // per LLM: calls, busy, active
     __shared__ uint32_t s_valid, s_far;
-    const uint64_t lo = a.offsets[r], n = a.offsets[r + 1] - lo;
+    uint64_t lo, n;
+    (void)trace_calls(a, r, lo, n);
     if (n == 0 || (!Global && n > a.lds_cap))
         return;                                        // empty, or the global pass takes it
     uint32_t P = kThreads;                              // padded length: a power of two
@@ -630,8 +677,8 @@ __device__ __forceinline__ void one_trace(const StatsArgs &a, uint32_t r, uint32
             constexpr int E = decltype(e_const)::value;
             uint64_t k[E];
             uint32_t kb = 0, kv = 0;
-            bool far = false;
-            load_keys<E, kThreads>(a, lo, n, threadIdx.x, base, k, kb, kv, far);
+            bool far = false, falls = false;
+            load_keys<E, kThreads>(a, lo, n, threadIdx.x, base, k, kb, kv, far, falls);
             if (kb)
                 atomicOr(flags, kb);
             const uint32_t wv = wave_sum_u32(kv);
@@ -741,8 +788,8 @@ __global__ void __launch_bounds__(64 * kSweepWaves) trace_sweep_kernel(StatsArgs
         (int)(blockIdx.x * kSweepWaves + (threadIdx.x >> 6)));
     if (r >= a.R)
         return;                                        // uniform over the wave
-    const uint64_t lo = a.offsets[r], n64 = a.offsets[r + 1] - lo;
-    if (n64 == 0 || n64 > a.lds_cap)
+    uint64_t lo, n64;
+    if (!short_trace(a, r, lane, lo, n64))
         return;                                        // empty, or the global pass takes it
     const uint32_t n = (uint32_t)n64, M = a.M, rows = (n + 63) >> 6;
     const uint64_t E = a.end[lo + n - 1];
@@ -837,10 +884,11 @@ __global__ void __launch_bounds__(64 * kSweepWaves) trace_sweep_kernel(StatsArgs
 // a block's own atomics have completed (its vector memory count drained) before it counts
 // itself, so no cache needs writing back or invalidating (a device-wide fence per block would
 // cost both for every block).  Status bits: 1 llm out of range, 2 end before start, 4 start or
-// duration out of range, 8 a result beyond 2^31 - 1 (it could not be loaded as an ALP input).
+// duration out of range, 8 a result beyond 2^31 - 1 (it could not be loaded as an ALP input), 16
+// bad offsets.
 __device__ __forceinline__ void finish_block(const StatsArgs &a, uint32_t i, uint32_t P)
 {
-    __shared__ uint32_t s_last, s_flags;
+    __shared__ uint32_t s_last, s_flags, s_longs, s_measure[2];
     __shared__ unsigned long long s_tot[3 * ALP_MAX_LLMS];
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's atomics are done
     __syncthreads();
@@ -857,13 +905,40 @@ __device__ __forceinline__ void finish_block(const StatsArgs &a, uint32_t i, uin
             }
         }
         s_last = last;
-        s_flags = 0;
+        s_longs = last && !a.planned ? atomicExch(a.long_count, 0u) : 0u;
+        s_flags = s_measure[0] = s_measure[1] = 0;
     }
     if (threadIdx.x < 3 * ALP_MAX_LLMS)
         s_tot[threadIdx.x] = 0;
     __syncthreads();
     if (!s_last)
         return;                                        // uniform over the block
+    auto report = [&](uint32_t flags) {
+        StatsTail t = {};
+        t.flags = flags;
+        t.listed = atomicExch(a.work_count, 0u);
+        t.longs = s_longs;
+        t.longest = s_measure[0];
+        t.in_order = s_measure[1];
+        StatsTail *dst = reinterpret_cast<StatsTail *>(a.out + ALP_MAX_LLMS);
+        *dst = t;
+        __hip_atomic_store(&dst->seq, a.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    };
+    // The measures, then (unless long traces are still to come) the sums.
+    for (uint32_t k = threadIdx.x; k < 2 * kStatsCopies; k += kThreads) {
+        const uint32_t v = (uint32_t)atomicExch(
+            a.totals + (uint64_t)(k >> 1) * kStatsCopyStride + kLongestWord + (k & 1), 0ull);
+        if (k & 1)
+            atomicAdd(&s_measure[1], v);
+        else
+            atomicMax(&s_measure[0], v);
+    }
+    __syncthreads();
+    if (s_longs) {
+        if (threadIdx.x == 0)
+            report(atomicOr(a.flags, 0u));
+        return;
+    }
     const uint32_t W = 3 * a.M;
     for (uint32_t k = threadIdx.x; k < kStatsCopies * W; k += kThreads) {
         const uint32_t c = k / W, f = k - c * W;
@@ -896,15 +971,11 @@ __device__ __forceinline__ void finish_block(const StatsArgs &a, uint32_t i, uin
         st.calls = calls;
         st.busy_us = busy;
         st.active_us = active;
-        a.out[m] = st;
+        a.out[m] = st;                                 // (the wave that stores the tail's signal)
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        StatsTail t = {};
-        t.flags = atomicExch(a.flags, 0u) | s_flags;
-        t.listed = atomicExch(a.work_count, 0u);
-        *reinterpret_cast<StatsTail *>(a.out + ALP_MAX_LLMS) = t;
-    }
+    if (threadIdx.x == 0)
+        report(atomicExch(a.flags, 0u) | s_flags);
 }
 
 constexpr uint32_t kWaveSortWaves = 4;       // traces per workgroup of the direct sort
@@ -923,10 +994,13 @@ __device__ __forceinline__ void wave_trace(const StatsArgs &a, uint32_t r, uint6
     const uint64_t base = a.start[lo] - (1ull << 28);      // modulo 2^64
     uint64_t k[E];
     uint32_t bad = 0, valid = 0;
-    bool far = false;
-    load_keys<E, 64>(a, lo, n, lane, base, k, bad, valid, far);
+    bool far = false, falls = false;
+    load_keys<E, 64>(a, lo, n, lane, base, k, bad, valid, far, falls);
     if (bad)
         atomicOr(a.flags, bad);
+    unsigned long long *copy = a.totals + (uint64_t)(r % kStatsCopies) * kStatsCopyStride;
+    if (!__ballot(falls) && lane == 0)
+        atomicAdd(&copy[kInOrderWord], 1ull);
     if (__ballot(far)) {
         if (lane == 0)
             a.work[atomicAdd(a.work_count, 1u)] = r;
@@ -939,7 +1013,6 @@ __device__ __forceinline__ void wave_trace(const StatsArgs &a, uint32_t r, uint6
     if (lane < 3 * M)
         s_sum[lane] = 0;
     group_sweep_regs<E, 64>(k, nvalid, base, s_sum, lane);
-    unsigned long long *copy = a.totals + (uint64_t)(r % kStatsCopies) * kStatsCopyStride;
     if (lane < 3 * M) {
         const unsigned long long v = s_sum[lane];
         if (v)
@@ -958,9 +1031,17 @@ __global__ void __launch_bounds__(64 * kWaveSortWaves) trace_wave_kernel(StatsAr
         (int)(blockIdx.x * kWaveSortWaves + wave));
     if (r >= a.R)
         return;                                        // uniform over the wave
-    const uint64_t lo = a.offsets[r], n64 = a.offsets[r + 1] - lo;
-    if (n64 == 0 || n64 > a.lds_cap || n64 > kWaveSortMax)
+    uint64_t lo, n64;
+    if (!short_trace(a, r, lane, lo, n64))
         return;                                        // empty, or another pass takes it
+    if (n64 > kWaveSortMax) {
+        if (n64 > a.group_max && lane == 0)            // no group was launched for it
+            a.work[atomicAdd(a.work_count, 1u)] = r;
+        if (lane == 0)
+            atomicMax(&a.totals[(uint64_t)(r % kStatsCopies) * kStatsCopyStride + kLongestWord],
+                      (unsigned long long)n64);
+        return;
+    }
     const uint32_t n = (uint32_t)n64;
     unsigned long long *sum = s_sum[wave];
     if (n <= 64)
@@ -984,11 +1065,12 @@ __global__ void __launch_bounds__(NT) trace_group_kernel(StatsArgs a)
     constexpr uint32_t P = NT * E;
     __shared__ uint64_t s_buf[P];
     __shared__ unsigned long long s_sum[3 * ALP_MAX_LLMS];
-    __shared__ uint32_t s_valid, s_far;
+    __shared__ uint32_t s_valid, s_far, s_falls;
     const uint32_t r = blockIdx.x, t = threadIdx.x;
     if (r >= a.R)
         return;                                        // uniform over the block
-    const uint64_t lo = a.offsets[r], n64 = a.offsets[r + 1] - lo;
+    uint64_t lo, n64;
+    (void)trace_calls(a, r, lo, n64);
     if (n64 <= (uint64_t)LO || n64 > a.lds_cap)
         return;                                        // another pass takes it
     if (n64 > P) {
@@ -1002,6 +1084,7 @@ __global__ void __launch_bounds__(NT) trace_group_kernel(StatsArgs a)
     if (t == 0) {
         s_valid = 0;
         s_far = 0;
+        s_falls = 0;
     }
     if (t < 3 * M)
         s_sum[t] = 0;
@@ -1009,18 +1092,22 @@ __global__ void __launch_bounds__(NT) trace_group_kernel(StatsArgs a)
     const uint64_t base = a.start[lo] - (1ull << 28);      // modulo 2^64
     uint64_t k[E];
     uint32_t bad = 0, valid = 0;
-    bool far = false;
-    load_keys<E, NT>(a, lo, n, t, base, k, bad, valid, far);
+    bool far = false, falls = false;
+    load_keys<E, NT>(a, lo, n, t, base, k, bad, valid, far, falls);
     if (bad)
         atomicOr(a.flags, bad);
     const uint32_t wvalid = wave_sum_u32(valid);
-    const bool wfar = __ballot(far) != 0;
+    const bool wfar = __ballot(far) != 0, wfalls = __ballot(falls) != 0;
     if ((t & 63) == 0) {
         atomicAdd(&s_valid, wvalid);
         if (wfar)
             atomicOr(&s_far, 1u);
+        if (wfalls)
+            atomicOr(&s_falls, 1u);
     }
     __syncthreads();
+    if (t == 0 && !s_falls)
+        atomicAdd(&a.totals[(uint64_t)(r % kStatsCopies) * kStatsCopyStride + kInOrderWord], 1ull);
     if (s_far) {                                       // uniform over the block
         if (t == 0)
             a.work[atomicAdd(a.work_count, 1u)] = r;
@@ -1068,68 +1155,71 @@ __global__ void __launch_bounds__(kThreads) trace_sort_kernel(StatsArgs a)
 __global__ void __launch_bounds__(kThreads) trace_long_kernel(StatsArgs a)
 {
     one_trace<kLong>(a, a.long_traces[blockIdx.x], blockIdx.x, nullptr);
-    const uint32_t P = sort_participants(a);           // the list is still intact here
+    // the list is still intact here (no sort launch: its blocks have finished before)
+    const uint32_t P = a.sort_grid ? sort_participants(a) : 0u;
     finish_block(a, P + blockIdx.x, P + a.num_long);
 }
 
 }  // namespace
 
-hipError_t launch_trace_stats(uint32_t M, uint32_t R, const uint64_t *offsets, const uint32_t *llm,
-                              const uint64_t *start, const uint64_t *end, uint32_t lds_cap,
-                              uint32_t max_short, uint32_t num_long, const uint32_t *long_traces,
-                              const uint64_t *long_base, uint64_t *scratch, uint64_t *totals,
-                              uint32_t *work, bool sweep, bool zero_first, alp_stats_t *out,
-                              hipStream_t st)
+hipError_t launch_trace_stats(const StatsLaunch &l, hipStream_t st)
 {
     hipError_t e;
-    if (zero_first) {
-        hipLaunchKernelGGL(stats_init_kernel, dim3(1), dim3(256), 0, st, totals,
+    const uint32_t R = l.R;
+    if (l.zero_first) {
+        hipLaunchKernelGGL(stats_init_kernel, dim3(1), dim3(256), 0, st, l.totals,
                            kStatsTotalsWords + kStatsTailWords);
         if ((e = hipGetLastError()) != hipSuccess)
             return e;
     }
     StatsArgs a;
-    a.M = M;
-    a.lds_cap = lds_cap;
+    a.M = l.M;
+    a.lds_cap = l.lds_cap;
     a.R = R;
-    a.offsets = offsets;
-    a.llm = llm;
-    a.start = start;
-    a.end = end;
-    a.long_traces = long_traces;
-    a.long_base = long_base;
-    a.scratch = scratch;
-    a.totals = reinterpret_cast<unsigned long long *>(totals);
-    a.flags = reinterpret_cast<uint32_t *>(totals + kStatsTotalsWords);
-    a.work = work;
-    a.work_count = reinterpret_cast<uint32_t *>(totals + kStatsTotalsWords + 1);
-    a.done = reinterpret_cast<uint32_t *>(totals + kStatsTotalsWords + 1) + 1;
-    a.slot_done = reinterpret_cast<uint32_t *>(totals + kStatsTotalsWords + 2);
-    a.out = out;
-    if (sweep) {
+    a.offsets = l.offsets;
+    a.llm = l.llm;
+    a.start = l.start;
+    a.end = l.end;
+    a.long_traces = l.long_traces;
+    a.long_base = l.long_base;
+    a.scratch = l.scratch;
+    a.totals = reinterpret_cast<unsigned long long *>(l.totals);
+    a.flags = reinterpret_cast<uint32_t *>(l.totals + kStatsTotalsWords);
+    a.long_count = a.flags + 1;
+    a.work = l.work;
+    a.work_count = reinterpret_cast<uint32_t *>(l.totals + kStatsTotalsWords + 1);
+    a.done = a.work_count + 1;
+    a.slot_done = reinterpret_cast<uint32_t *>(l.totals + kStatsTotalsWords + 2);
+    a.out = l.out;
+    a.planned = l.planned ? 1u : 0u;
+    a.seq = l.seq;
+    a.num_long = l.num_long;
+    a.group_max = l.max_short > 1536 ? 2048u : l.max_short > 1024 ? 1536u
+                : l.max_short > kWaveSortMax ? 1024u : kWaveSortMax;
+    if (l.order == kStatsSweep) {
         const dim3 grid((R + kSweepWaves - 1) / kSweepWaves), block(64 * kSweepWaves);
-        if (M <= 2)
+        if (l.M <= 2)
             hipLaunchKernelGGL(trace_sweep_kernel<2>, grid, block, 0, st, a);
-        else if (M <= 4)
+        else if (l.M <= 4)
             hipLaunchKernelGGL(trace_sweep_kernel<4>, grid, block, 0, st, a);
         else
             hipLaunchKernelGGL(trace_sweep_kernel<ALP_MAX_LLMS>, grid, block, 0, st, a);
         if ((e = hipGetLastError()) != hipSuccess)
             return e;
-    } else {
-        if (max_short > 1536) {
+    } else if (l.order == kStatsDirect) {
+        if (a.group_max > 1536) {
             hipLaunchKernelGGL(HIP_KERNEL_NAME(trace_group_kernel<8, 256, 1536>), dim3(R),
                                dim3(256), 0, st, a);
             if ((e = hipGetLastError()) != hipSuccess)
                 return e;
         }
-        if (max_short > 1024) {
+        if (a.group_max > 1024) {
             hipLaunchKernelGGL(HIP_KERNEL_NAME(trace_group_kernel<8, 192, 1024>), dim3(R),
                                dim3(192), 0, st, a);
             if ((e = hipGetLastError()) != hipSuccess)
                 return e;
         }
-        if (max_short > kWaveSortMax) {
+        if (a.group_max > kWaveSortMax) {
             hipLaunchKernelGGL(HIP_KERNEL_NAME(trace_group_kernel<8, 128, kWaveSortMax>),
                                dim3(R), dim3(128), 0, st, a);
             if ((e = hipGetLastError()) != hipSuccess)
@@ -1140,17 +1230,18 @@ hipError_t launch_trace_stats(uint32_t M, uint32_t R, const uint64_t *offsets, c
         if ((e = hipGetLastError()) != hipSuccess)
             return e;
     }
-    // The work list's length is known only on the device: a grid of at most kSortBlocks
-    // blocks takes its entries in turn (an empty list costs one short launch).
-    const size_t lds = (size_t)2 * lds_cap * sizeof(uint64_t);
-    const uint32_t sort_blocks = R > kSortBlocks ? kSortBlocks : R;
-    a.sort_grid = sort_blocks;
-    a.num_long = num_long;
-    hipLaunchKernelGGL(trace_sort_kernel, dim3(sort_blocks), dim3(kThreads), lds, st, a);
-    if ((e = hipGetLastError()) != hipSuccess)
-        return e;
-    if (num_long) {
-        hipLaunchKernelGGL(trace_long_kernel, dim3(num_long), dim3(kThreads), 0, st, a);
+    a.sort_grid = 0;
+    if (l.order != kStatsLongOnly) {
+        // The work list's length is known only on the device: a grid of at most kSortBlocks
+        // blocks takes its entries in turn (an empty list costs one short launch).
+        const size_t lds = (size_t)2 * l.lds_cap * sizeof(uint64_t);
+        a.sort_grid = R > kSortBlocks ? kSortBlocks : R;
+        hipLaunchKernelGGL(trace_sort_kernel, dim3(a.sort_grid), dim3(kThreads), lds, st, a);
+        if ((e = hipGetLastError()) != hipSuccess)
+            return e;
+    }
+    if (l.num_long) {
+        hipLaunchKernelGGL(trace_long_kernel, dim3(l.num_long), dim3(kThreads), 0, st, a);
         if ((e = hipGetLastError()) != hipSuccess)
             return e;
     }

@@ -1,0 +1,80 @@
+"""The statistics' launch sequences on one context, on an MI355X: the sweep, the switch to the direct
+sort and back, long traces found by the kernels and then expected, traces longer than the last
+direct call's, and offsets that only the kernels see.  Every result equals the oracle's."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+from workloads.traces import make_traces
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def alp():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2604_15186_amd import alp as binding
+    binding.lib()
+    return binding
+
+
+def _shuffle(tr, seed):
+    rng = np.random.default_rng(seed)
+    off = tr["offsets"].astype(np.int64)
+    perm = np.concatenate([lo + rng.permutation(hi - lo) for lo, hi in zip(off[:-1], off[1:])])
+    return {**tr, **{k: tr[k][perm] for k in ("llm", "start", "end")}}
+
+
+def _joined(tr, per):
+    """The traces joined `per` at a time (longer traces of the same calls)."""
+    return {**tr, "offsets": np.append(tr["offsets"][:-1:per], tr["offsets"][-1:])}
+
+
+def _same(ctx, tr):
+    args = (tr["M"], tr["offsets"], tr["llm"], tr["start"], tr["end"])
+    got, want = ctx.compute(*args), oracle.trace_stats(*args)
+    for f in want.dtype.names:
+        assert [int(v) for v in got[f]] == [int(v) for v in want[f]], f
+
+
+def _one_start(tr):
+    """Every trace moved to the same start, so that joined traces span a few minutes."""
+    off = tr["offsets"].astype(np.int64)
+    first = np.repeat(np.minimum.reduceat(tr["start"], off[:-1]), np.diff(off))
+    return {**tr, "start": tr["start"] - first, "end": tr["end"] - first}
+
+
+@pytest.mark.parametrize("shape,R,per", [("rag", 700, 40), ("beam", 90, 1), ("beam", 200, 3)])
+def test_one_context_takes_every_path(alp, shape, R, per):
+    logged = make_traces(shape, R, 31)
+    mixed = _shuffle(logged, 1)
+    longer = _shuffle(_joined(_one_start(logged), per), 2)   # beam, 3 at a time: some beyond 2,048
+    with alp.StatsContext(0) as ctx:
+        for tr in (logged, mixed, mixed, longer, mixed, longer, longer, logged, logged, mixed,
+                   longer, logged, longer):
+            _same(ctx, tr)
+
+
+@pytest.mark.parametrize("offsets", [[0, 100, 10], [0, 4, 3, 10], [5, 10], [0, 12, 11, 10],
+                                     [3, 2, 1], [0, 5, (1 << 63), 10]])
+def test_bad_offsets_are_refused_and_leave_the_context_working(alp, offsets):
+    """The call arrays hold offsets[-1] entries: no pass reads a call beyond them."""
+    good = make_traces("rag", 50, 3)
+    calls = int(offsets[-1])
+    rng = np.random.default_rng(4)
+    start = rng.integers(0, 1000, calls).astype(np.uint64)
+    bad = (3, np.asarray(offsets, np.uint64), np.zeros(calls, np.uint32), start, start + 5)
+    with alp.StatsContext(0) as ctx:
+        for order in (good, _shuffle(good, 5)):           # from the sweep, then the direct sort
+            for _ in range(2):
+                _same(ctx, order)
+            for _ in range(2):
+                with pytest.raises(alp.AlpError) as err:
+                    ctx.compute(*bad)
+                long = offsets[1] + (1 << 24) < offsets[2] if len(offsets) > 3 else False
+                assert err.value.status == (alp.ALP_ERANGE if long else alp.ALP_EINVAL)
+            _same(ctx, order)

@@ -138,94 +138,14 @@ __device__ __forceinline__ void bitonic_sort(uint64_t *key, uint64_t *val, uint3
     }
 }
 
-// One compare-exchange of the bitonic network seen from one side: keep the minimum (else the
-// maximum) of the own and the partner's key.
+// One compare-exchange seen from one side: keep the minimum (else the maximum) of the own and the
+// partner's key.
 __device__ __forceinline__ uint64_t keep_one(uint64_t mine, uint64_t other, bool keep_min)
 {
     // other < mine selects the minimum where keep_min holds; elsewhere it keeps mine unless
     // other is larger (equal keys: either is the same value).  One compare and a mask test.
     const bool take = (other < mine) == keep_min;
     return take ? other : mine;
-}
-
-// Position i is the pair's lower index iff bit `stride` of i is clear, and lies in a run of
-// `size` sorted ascending iff bit `size` of i is clear; the lower index of an ascending pair,
-// or the upper of a descending one, keeps the minimum.
-__device__ __forceinline__ bool keeps_min(uint32_t i, uint32_t stride, uint32_t size)
-{
-    return ((i & stride) == 0) == ((i & size) == 0);
-}
-
-// Exchanges with partner lane (lane ^ Q) for stride Q * E, if that stride occurs in this run.
-template <int E, int Q>
-__device__ __forceinline__ void lane_stage(uint64_t (&k)[E], uint32_t size, uint32_t t)
-{
-    constexpr uint32_t stride = (uint32_t)(Q * E);
-    if (2 * stride > size)
-        return;
-    const bool km = keeps_min(t * E, stride, size);   // the same for all E slots
-    // Partners of up to 4 slots fetched before any is used: the cross-lane moves' latency
-    // overlaps.
-#pragma unroll
-    for (int e0 = 0; e0 < E; e0 += 4) {
-        uint64_t o[4];
-#pragma unroll
-        for (int e = e0; e < e0 + 4 && e < E; ++e)
-            o[e - e0] = lane_xor64<Q>(k[e]);
-#pragma unroll
-        for (int e = e0; e < e0 + 4 && e < E; ++e)
-            k[e] = keep_one(k[e], o[e - e0], km);
-    }
-}
-
-// Bitonic sort of P = NT E keys held E per thread of NT in registers, ascending by position:
-// thread t holds positions t E .. t E + E - 1 (a sort within one wave takes NT = 64 and t = the
-// lane, so that no exchange reaches another wave).  An exchange whose partner is in the same
-// thread runs in registers, one whose partner is in the same wave by cross-lane moves (lane ^
-// stride / E), and only those whose partner is in another wave go through LDS, in a layout
-// (slot e of thread t at e * NT + t) where a wave's 64 accesses are consecutive; two LDS
-// buffers alternate, so each such exchange needs one barrier.  buf holds 2 P keys.
-template <int E, int NT = kThreads>
-__device__ __forceinline__ void bitonic_sort_regs(uint64_t (&k)[E], uint64_t *buf, uint32_t P,
-                                                  uint32_t t)
-{
-    uint32_t flip = 0;
-    for (uint32_t size = 2; size <= P; size <<= 1) {
-        for (uint32_t stride = size >> 1; stride >= (uint32_t)E * 64; stride >>= 1) {
-            uint64_t *b = buf + flip * P;
-            flip ^= 1u;
-#pragma unroll
-            for (int e = 0; e < E; ++e)
-                b[e * NT + t] = k[e];
-            __syncthreads();
-            const uint32_t pt = t ^ (stride / E);
-            const bool km = keeps_min(t * E, stride, size);
-#pragma unroll
-            for (int e = 0; e < E; ++e)
-                k[e] = keep_one(k[e], b[e * NT + pt], km);
-        }
-        lane_stage<E, 32>(k, size, t);
-        lane_stage<E, 16>(k, size, t);
-        lane_stage<E, 8>(k, size, t);
-        lane_stage<E, 4>(k, size, t);
-        lane_stage<E, 2>(k, size, t);
-        lane_stage<E, 1>(k, size, t);
-#pragma unroll
-        for (int st = E / 2; st >= 1; st >>= 1) {
-            if ((uint32_t)(2 * st) > size)
-                continue;
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                if (e & st)
-                    continue;
-                const uint64_t a = k[e], b = k[e | st];
-                const bool asc = ((t * E + e) & size) == 0;
-                const bool swap = (a > b) == asc;         // equal keys: either way
-                k[e] = swap ? b : a;
-                k[e | st] = swap ? a : b;
-            }
-        }
-    }
 }
 
 // The sweep over the sorted calls of one trace: each thread takes a contiguous chunk of the
@@ -429,6 +349,44 @@ constexpr uint32_t pow2_at_least(uint32_t v)
     return p;
 }
 
+// Keys as double-precision floats (FLOAT below).  A key below the infinity's pattern is a finite
+// non-negative double, those order like integers, and minimum and maximum (denormals are kept) are
+// one instruction each where a 64-bit integer exchange takes a compare and four selections.  Keys
+// of LLMs 0 to 2 (llm << 61 and 61 bits below) qualify, padded with the infinity.
+constexpr uint32_t kFloatLlms = 3;
+template <bool FLOAT>
+constexpr uint64_t kKeyPad = FLOAT ? 0x7FF0000000000000ull : kPad;
+
+__device__ __forceinline__ uint64_t min_f64(uint64_t a, uint64_t b)
+{
+    uint64_t d;
+    asm("v_min_f64 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+    return d;
+}
+
+__device__ __forceinline__ uint64_t max_f64(uint64_t a, uint64_t b)
+{
+    uint64_t d;
+    asm("v_max_f64 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+    return d;
+}
+
+// min(a, -b)
+__device__ __forceinline__ uint64_t min_neg_f64(uint64_t a, uint64_t b)
+{
+    uint64_t d;
+    asm("v_min_f64 %0, %1, -%2" : "=v"(d) : "v"(a), "v"(b));
+    return d;
+}
+
+template <int E>
+__device__ __forceinline__ void flip_signs(uint64_t (&k)[E], uint32_t mask)
+{
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        k[e] ^= (uint64_t)mask << 32;
+}
+
 // One stage of a bitonic network whose comparators all put the minimum at the lower position:
 // the first stage of a merge of SIZE pairs position i with its mirror i ^ (SIZE - 1) (MIRROR),
 // the later ones with i ^ STRIDE.  Positions t E + e of NT threads, E keys each (E, NT powers of
@@ -436,8 +394,15 @@ constexpr uint32_t pow2_at_least(uint32_t v)
 // upper position lies there leaves the lower one as it is.  Partners in the same thread are
 // exchanged in registers, in the same wave across lanes, in other waves through buf (NT E keys,
 // two barriers).
-template <int E, int NT, int SIZE, int STRIDE, bool MIRROR>
-__device__ __forceinline__ void mirror_stage(uint64_t (&k)[E], uint64_t *buf, uint32_t t)
+//
+// Across lanes with FLOAT: the upper lanes of a stage hold their keys negated (signs: the sign bit
+// of the lane's present state).  A lower lane takes min(mine, -partner's) of the upper one's negated
+// key, an upper lane the same of its negated and the partner's plain key, -max: one instruction on
+// both sides, where selecting by side takes a compare and two.  Exchanges in registers and through
+// buf find every key plain.
+template <bool FLOAT, int E, int NT, int SIZE, int STRIDE, bool MIRROR>
+__device__ __forceinline__ void mirror_stage(uint64_t (&k)[E], uint64_t *buf, uint32_t t,
+                                             uint32_t &signs)
 {
     // partner of (t, e): thread t ^ TQ, register e ^ EQ
     constexpr uint32_t D = MIRROR ? SIZE - 1 : STRIDE;       // position xor
@@ -450,13 +415,23 @@ __device__ __forceinline__ void mirror_stage(uint64_t (&k)[E], uint64_t *buf, ui
                 continue;
             const int f = e ^ (int)EQ;
             const uint64_t a = k[e], b = k[f];
-            const bool swap = a > b;
-            k[e] = swap ? b : a;
-            k[f] = swap ? a : b;
+            if constexpr (FLOAT) {
+                k[e] = min_f64(a, b);
+                k[f] = max_f64(a, b);
+            } else {
+                const bool swap = a > b;
+                k[e] = swap ? b : a;
+                k[f] = swap ? a : b;
+            }
         }
     } else {
         const bool lower = (t & (HALF / E)) == 0;
         if constexpr (TQ < 64) {
+            if constexpr (FLOAT) {
+                const uint32_t s = (t * (0x80000000u / (HALF / E))) & 0x80000000u;
+                flip_signs(k, signs ^ s);
+                signs = s;
+            }
             // Every partner value is fetched before any key changes: with EQ != 0 a key's
             // partner register may come earlier in the loop.
             uint64_t o[E];
@@ -465,8 +440,12 @@ __device__ __forceinline__ void mirror_stage(uint64_t (&k)[E], uint64_t *buf, ui
                 o[e] = lane_xor_any64<TQ>(k[e ^ EQ]);
 #pragma unroll
             for (int e = 0; e < E; ++e)
-                k[e] = keep_one(k[e], o[e], lower);
+                k[e] = FLOAT ? min_neg_f64(k[e], o[e]) : keep_one(k[e], o[e], lower);
         } else {
+            if constexpr (FLOAT && E == 1) {           // (E > 1: plain after the registers' stages)
+                flip_signs(k, signs);
+                signs = 0;
+            }
 #pragma unroll
             for (int e = 0; e < E; ++e)
                 buf[e * NT + t] = k[e];
@@ -482,89 +461,102 @@ __device__ __forceinline__ void mirror_stage(uint64_t (&k)[E], uint64_t *buf, ui
     }
 }
 
-template <int E, int NT, int SIZE, int STRIDE>
-__device__ __forceinline__ void mirror_strides(uint64_t (&k)[E], uint64_t *buf, uint32_t t)
+template <bool FLOAT, int E, int NT, int SIZE, int STRIDE>
+__device__ __forceinline__ void mirror_strides(uint64_t (&k)[E], uint64_t *buf, uint32_t t,
+                                               uint32_t &signs)
 {
     if constexpr (STRIDE >= 1) {
-        mirror_stage<E, NT, SIZE, STRIDE, false>(k, buf, t);
-        mirror_strides<E, NT, SIZE, STRIDE / 2>(k, buf, t);
+        if constexpr (FLOAT && STRIDE < E && 2 * STRIDE >= E && SIZE > E) {
+            flip_signs(k, signs);                  // the first exchange in registers of the merge
+            signs = 0;
+        }
+        mirror_stage<FLOAT, E, NT, SIZE, STRIDE, false>(k, buf, t, signs);
+        mirror_strides<FLOAT, E, NT, SIZE, STRIDE / 2>(k, buf, t, signs);
     }
+}
+
+template <bool FLOAT, int E, int NT, int SIZE>
+__device__ __forceinline__ void mirror_merges(uint64_t (&k)[E], uint64_t *buf, uint32_t t,
+                                              uint32_t &signs)
+{
+    mirror_stage<FLOAT, E, NT, SIZE, SIZE / 2, true>(k, buf, t, signs);
+    mirror_strides<FLOAT, E, NT, SIZE, SIZE / 4>(k, buf, t, signs);
+    if constexpr (SIZE < (int)pow2_at_least(NT * E))
+        mirror_merges<FLOAT, E, NT, SIZE * 2>(k, buf, t, signs);
 }
 
 // Ascending sort of the NT E keys (E per thread, thread t at positions t E ..), padded virtually
 // to the next power of two: every merge of SIZE = 2, 4, .. is a mirror stage and half-cleaners.
-template <int E, int NT, int SIZE = 2>
+template <bool FLOAT, int E, int NT>
 __device__ __forceinline__ void mirror_sort_regs(uint64_t (&k)[E], uint64_t *buf, uint32_t t)
 {
-    mirror_stage<E, NT, SIZE, SIZE / 2, true>(k, buf, t);
-    mirror_strides<E, NT, SIZE, SIZE / 4>(k, buf, t);
-    if constexpr (SIZE < (int)pow2_at_least(NT * E))
-        mirror_sort_regs<E, NT, SIZE * 2>(k, buf, t);
+    uint32_t signs = 0;
+    mirror_merges<FLOAT, E, NT, 2>(k, buf, t, signs);
+    if constexpr (FLOAT && E == 1)
+        flip_signs(k, signs);                      // (E > 1: the last exchanges left them plain)
 }
 
 // Per-LLM calls, durations and covered time of one trace's sorted keys, held by a group of NT
 // threads (one wave, NT = 64, or a workgroup), added to s_sum: thread t holds positions
-// t E .. t E + E - 1 of the valid calls and padding.  An exclusive prefix maximum of
-// (llm << 61 | end) over the positions before a call tells whether an earlier call of the same
-// LLM exists and the furthest end among them; the call adds its part beyond that end.  Key of a call: (llm << 61 | start - base
-// << 32 | duration), the field start - base below 2^29.  The calls' fields are unpacked again
-// where they are used rather than held, so that large E keep few registers.
-template <int E, int NT>
+// t E .. t E + E - 1 of the valid calls and padding.  Key of a call: (llm << 61 | start - base << 32
+// | duration), the field start - base below 2^29.  The exclusive prefix maximum of (llm << 61 | end)
+// over the positions before a call, taken with its own (llm << 61 | start), is where its part not
+// covered by earlier calls of its LLM begins.  The fields are unpacked where they are used rather
+// than held, so that large E keep few registers.
+template <bool FLOAT, int E, int NT>
 __device__ __forceinline__ void group_sweep_regs(const uint64_t (&k)[E], uint32_t valid,
-                                                 uint64_t base, unsigned long long *s_sum,
-                                                 uint32_t t)
+                                                 unsigned long long *s_sum, uint32_t t)
 {
     const uint32_t first = t * E;
-    auto llm_of = [](uint64_t kk) { return (uint32_t)(kk >> 61); };
-    auto start_of = [&](uint64_t kk) { return base + ((kk >> 32) & ((1ull << 29) - 1)); };
-    auto end_of = [&](uint64_t kk) { return start_of(kk) + (kk & 0xFFFFFFFFull); };
+    auto larger = [](uint64_t x, uint64_t y) { return FLOAT ? max_f64(x, y) : x > y ? x : y; };
+    // (llm << 61 | start) and (llm << 61 | end), the times relative to the keys' base
+    auto start_of = [](uint64_t kk) {
+        const uint32_t h = (uint32_t)(kk >> 32);
+        return ((uint64_t)(h & 0xE0000000u) << 32) | (h & 0x1FFFFFFFu);
+    };
     uint64_t run = 0;
 #pragma unroll
-    for (int j = 0; j < E; ++j) {
-        if (first + j < valid) {
-            const uint64_t pk = ((uint64_t)llm_of(k[j]) << 61) | end_of(k[j]);
-            run = pk > run ? pk : run;
-        }
-    }
+    for (int j = 0; j < E; ++j)
+        if (first + j < valid)
+            run = larger(run, start_of(k[j]) + (uint32_t)k[j]);
     uint64_t prev;
     if constexpr (NT == 64)
         prev = wave_exclusive_max(run, t);
     else
         prev = block_exclusive_max(run);
-    constexpr uint64_t kLow61 = (1ull << 61) - 1;
-    uint32_t cur = ~0u;
-    uint64_t c_calls = 0, c_busy = 0, c_active = 0;
+    uint32_t cur = ~0u, c_calls = 0;
+    uint64_t c_busy = 0, c_active = 0;
+    auto flush = [&]() {
+        atomicAdd(&s_sum[3 * cur + 0], (unsigned long long)c_calls);
+        atomicAdd(&s_sum[3 * cur + 1], (unsigned long long)c_busy);
+        atomicAdd(&s_sum[3 * cur + 2], (unsigned long long)c_active);
+    };
 #pragma unroll
     for (int j = 0; j < E; ++j) {
         if (first + j >= valid)
             continue;                                  // (sorted: every later j too)
-        const uint32_t m = llm_of(k[j]);
-        const uint64_t s = start_of(k[j]), e = s + (k[j] & 0xFFFFFFFFull);
+        const uint32_t m = (uint32_t)(k[j] >> 61);
         if (m != cur) {
-            if (cur != ~0u) {
-                atomicAdd(&s_sum[3 * cur + 0], (unsigned long long)c_calls);
-                atomicAdd(&s_sum[3 * cur + 1], (unsigned long long)c_busy);
-                atomicAdd(&s_sum[3 * cur + 2], (unsigned long long)c_active);
-            }
-            c_calls = c_busy = c_active = 0;
+            if (cur != ~0u)
+                flush();
+            c_calls = 0;
+            c_busy = c_active = 0;
             cur = m;
         }
-        uint64_t from = s;
-        if ((prev >> 61) == m) {
-            const uint64_t reach = prev & kLow61;
-            from = reach > s ? reach : s;
-        }
+        // The furthest end before, if of this LLM, is above the start of its LLM's epoch; of a
+        // smaller LLM it is below every start here.
+        const uint64_t s = start_of(k[j]), e = s + (uint32_t)k[j];
+        const uint64_t from = larger(s, prev);
         c_calls += 1;
-        c_busy += e - s;
-        c_active += e > from ? e - from : 0;
-        const uint64_t pk = ((uint64_t)m << 61) | e;
-        prev = pk > prev ? pk : prev;
+        c_busy += (uint32_t)k[j];
+        if constexpr (FLOAT)
+            c_active += e - min_f64(e, from);
+        else
+            c_active += e > from ? e - from : 0;
+        prev = larger(prev, e);
     }
-    if (cur != ~0u) {
-        atomicAdd(&s_sum[3 * cur + 0], (unsigned long long)c_calls);
-        atomicAdd(&s_sum[3 * cur + 1], (unsigned long long)c_busy);
-        atomicAdd(&s_sum[3 * cur + 2], (unsigned long long)c_active);
-    }
+    if (cur != ~0u)
+        flush();
 }
 
 // Keys of the calls lo .. lo + n - 1 (n <= NT E) for thread t of a group of NT: calls j NT + t
@@ -575,7 +567,7 @@ __device__ __forceinline__ void group_sweep_regs(const uint64_t (&k)[E], uint32_
 // in groups of up to 4 keys, all in flight together and without branches: positions past the
 // trace load its last call again and become padding.  (A branch per call made the compiler
 // wait for each call's loads before the next; all E at once spill.)
-template <int E, int NT>
+template <bool FLOAT, int E, int NT>
 __device__ __forceinline__ void load_keys(const StatsArgs &a, uint64_t lo, uint32_t n, uint32_t t,
                                           uint64_t base, uint64_t (&k)[E], uint32_t &bad,
                                           uint32_t &valid, bool &far, bool &falls)
@@ -602,15 +594,16 @@ __device__ __forceinline__ void load_keys(const StatsArgs &a, uint64_t lo, uint3
             // In end order as far as a wave's own calls tell (its first has no neighbour here).
             const uint32_t en_lo = (uint32_t)en, before = dpp_mov<0x138>(en_lo, en_lo);
             falls = falls || (i < n && (int32_t)(en_lo - before) < 0);
-            const uint32_t b = m >= M ? 1u
-                             : en < st ? 2u
-                             : st >= kStartLimit || en - st >= kDurationLimit ? 4u : 0u;
-            const uint64_t off = st - base;
-            const bool ok = i < n && b == 0;
-            bad |= i < n ? b : 0u;
-            far = far || (ok && off >= (1ull << 29));
-            const bool use = ok && off < (1ull << 29);
-            k[j0 + g] = use ? ((uint64_t)m << 61) | (off << 32) | (en - st) : kPad;
+            const uint64_t off = st - base, dur = en - st;
+            // (a call that ends before it starts has a duration of 2^32 or more here)
+            const bool ok = m < M && (dur >> 32) == 0 && st < kStartLimit;
+            if (i < n && !ok)
+                bad |= m >= M ? 1u : en < st ? 2u : 4u;
+            const bool near = off < (1ull << 29);
+            far = far || (i < n && ok && !near);
+            const bool use = i < n && ok && near;
+            k[j0 + g] = use ? ((uint64_t)((m << 29) | (uint32_t)off) << 32) | (uint32_t)dur
+                            : kKeyPad<FLOAT>;
             valid += use ? 1u : 0u;
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -618,7 +611,7 @@ __device__ __forceinline__ void load_keys(const StatsArgs &a, uint64_t lo, uint3
 }
 
 // Statistics of trace r (slot = the block's trace slot in long_base for kLong) by one block.
-template <int Pass, int MM = ALP_MAX_LLMS>
+template <int Pass, bool FLOAT = false>
 __device__ __forceinline__ void one_trace(const StatsArgs &a, uint32_t r, uint32_t slot,
                                           unsigned char *s_dyn)
 {
@@ -678,7 +671,7 @@ __device__ __forceinline__ void one_trace(const StatsArgs &a, uint32_t r, uint32
             uint64_t k[E];
             uint32_t kb = 0, kv = 0;
             bool far = false, falls = false;
-            load_keys<E, kThreads>(a, lo, n, threadIdx.x, base, k, kb, kv, far, falls);
+            load_keys<FLOAT, E, kThreads>(a, lo, n, threadIdx.x, base, k, kb, kv, far, falls);
             if (kb)
                 atomicOr(flags, kb);
             const uint32_t wv = wave_sum_u32(kv);
@@ -696,8 +689,8 @@ __device__ __forceinline__ void one_trace(const StatsArgs &a, uint32_t r, uint32
             const uint32_t nvalid = s_valid;
             if (nvalid == 0)
                 return;
-            bitonic_sort_regs<E>(k, key, P, threadIdx.x);
-            group_sweep_regs<E, kThreads>(k, nvalid, base, s_sum, threadIdx.x);
+            mirror_sort_regs<FLOAT, E, kThreads>(k, key, threadIdx.x);
+            group_sweep_regs<FLOAT, E, kThreads>(k, nvalid, s_sum, threadIdx.x);
         };
         switch (P) {
         case kThreads: run(std::integral_constant<int, 1>{}); break;
@@ -924,28 +917,28 @@ __device__ __forceinline__ void finish_block(const StatsArgs &a, uint32_t i, uin
         *dst = t;
         __hip_atomic_store(&dst->seq, a.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     };
-    // The measures, then (unless long traces are still to come) the sums.
-    for (uint32_t k = threadIdx.x; k < 2 * kStatsCopies; k += kThreads) {
-        const uint32_t v = (uint32_t)atomicExch(
-            a.totals + (uint64_t)(k >> 1) * kStatsCopyStride + kLongestWord + (k & 1), 0ull);
-        if (k & 1)
-            atomicAdd(&s_measure[1], v);
+    // The measures and, unless long traces are still to come, the sums: every read in flight
+    // together.
+    const uint32_t W = s_longs ? 0u : 3 * a.M, F = W + 2;
+    for (uint32_t k = threadIdx.x; k < kStatsCopies * F; k += kThreads) {
+        const uint32_t c = k / F, f = k - c * F;
+        const uint32_t word = f < W ? f : kLongestWord + (f - W);
+        const unsigned long long v =
+            atomicExch(a.totals + (uint64_t)c * kStatsCopyStride + word, 0ull);
+        if (!v)
+            continue;
+        if (f < W)
+            atomicAdd(&s_tot[f], v);
+        else if (f == W)
+            atomicMax(&s_measure[0], (uint32_t)v);
         else
-            atomicMax(&s_measure[0], v);
+            atomicAdd(&s_measure[1], (uint32_t)v);
     }
-    __syncthreads();
     if (s_longs) {
+        __syncthreads();
         if (threadIdx.x == 0)
             report(atomicOr(a.flags, 0u));
         return;
-    }
-    const uint32_t W = 3 * a.M;
-    for (uint32_t k = threadIdx.x; k < kStatsCopies * W; k += kThreads) {
-        const uint32_t c = k / W, f = k - c * W;
-        const unsigned long long v =
-            atomicExch(a.totals + (uint64_t)c * kStatsCopyStride + f, 0ull);
-        if (v)
-            atomicAdd(&s_tot[f], v);
     }
     __syncthreads();
     const uint32_t m = threadIdx.x;
@@ -986,7 +979,7 @@ constexpr uint32_t kWaveSortMax = 64 * 8;    // longest trace one wave sorts (8 
 // per-LLM sums to s_sum (the wave's own) and then to the trace's copy of the totals.  Keys hold
 // a call's start relative to base = (first call's start) - 2^28; a trace with a valid call
 // outside [base, base + 2^29) goes to the work list for the block sort, which handles any span.
-template <int E>
+template <bool FLOAT, int E>
 __device__ __forceinline__ void wave_trace(const StatsArgs &a, uint32_t r, uint64_t lo, uint32_t n,
                                            uint32_t lane, unsigned long long *s_sum)
 {
@@ -995,7 +988,7 @@ __device__ __forceinline__ void wave_trace(const StatsArgs &a, uint32_t r, uint6
     uint64_t k[E];
     uint32_t bad = 0, valid = 0;
     bool far = false, falls = false;
-    load_keys<E, 64>(a, lo, n, lane, base, k, bad, valid, far, falls);
+    load_keys<FLOAT, E, 64>(a, lo, n, lane, base, k, bad, valid, far, falls);
     if (bad)
         atomicOr(a.flags, bad);
     unsigned long long *copy = a.totals + (uint64_t)(r % kStatsCopies) * kStatsCopyStride;
@@ -1009,10 +1002,10 @@ __device__ __forceinline__ void wave_trace(const StatsArgs &a, uint32_t r, uint6
     const uint32_t nvalid = wave_sum_u32(valid);
     if (nvalid == 0)
         return;
-    bitonic_sort_regs<E, 64>(k, nullptr, 64 * E, lane);
+    mirror_sort_regs<FLOAT, E, 64>(k, nullptr, lane);
     if (lane < 3 * M)
         s_sum[lane] = 0;
-    group_sweep_regs<E, 64>(k, nvalid, base, s_sum, lane);
+    group_sweep_regs<FLOAT, E, 64>(k, nvalid, s_sum, lane);
     if (lane < 3 * M) {
         const unsigned long long v = s_sum[lane];
         if (v)
@@ -1023,7 +1016,9 @@ __device__ __forceinline__ void wave_trace(const StatsArgs &a, uint32_t r, uint6
 // Every trace of at most 512 calls sorted directly (the context found most traces out of end
 // order): one wave per trace, kWaveSortWaves traces per workgroup; traces the wave does not take
 // (a span beyond its packed keys) are listed for the block sort that follows.
-__global__ void __launch_bounds__(64 * kWaveSortWaves) trace_wave_kernel(StatsArgs a)
+template <bool FLOAT>
+__global__ void __launch_bounds__(64 * kWaveSortWaves) __attribute__((amdgpu_waves_per_eu(8)))
+trace_wave_kernel(StatsArgs a)
 {
     __shared__ unsigned long long s_sum[kWaveSortWaves][3 * ALP_MAX_LLMS];
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1045,13 +1040,13 @@ __global__ void __launch_bounds__(64 * kWaveSortWaves) trace_wave_kernel(StatsAr
     const uint32_t n = (uint32_t)n64;
     unsigned long long *sum = s_sum[wave];
     if (n <= 64)
-        wave_trace<1>(a, r, lo, n, lane, sum);
+        wave_trace<FLOAT, 1>(a, r, lo, n, lane, sum);
     else if (n <= 128)
-        wave_trace<2>(a, r, lo, n, lane, sum);
+        wave_trace<FLOAT, 2>(a, r, lo, n, lane, sum);
     else if (n <= 256)
-        wave_trace<4>(a, r, lo, n, lane, sum);
+        wave_trace<FLOAT, 4>(a, r, lo, n, lane, sum);
     else
-        wave_trace<8>(a, r, lo, n, lane, sum);
+        wave_trace<FLOAT, 8>(a, r, lo, n, lane, sum);
 }
 
 // Every trace of LO + 1 to NT E calls sorted directly (8 keys per thread: 513 to 1,024 calls on
@@ -1059,7 +1054,7 @@ __global__ void __launch_bounds__(64 * kWaveSortWaves) trace_wave_kernel(StatsAr
 // trace, keyed and handed on as in trace_wave_kernel, sorted by mirror_sort_regs (exchanges
 // between waves through one LDS buffer of NT E keys).  8 keys per thread keep about 50 VGPRs;
 // 16 or 32 keys per lane needed 89 and 171 (2 to 5 waves per SIMD instead of 8).
-template <int E, int NT, int LO>
+template <bool FLOAT, int E, int NT, int LO>
 __global__ void __launch_bounds__(NT) trace_group_kernel(StatsArgs a)
 {
     constexpr uint32_t P = NT * E;
@@ -1093,7 +1088,7 @@ __global__ void __launch_bounds__(NT) trace_group_kernel(StatsArgs a)
     uint64_t k[E];
     uint32_t bad = 0, valid = 0;
     bool far = false, falls = false;
-    load_keys<E, NT>(a, lo, n, t, base, k, bad, valid, far, falls);
+    load_keys<FLOAT, E, NT>(a, lo, n, t, base, k, bad, valid, far, falls);
     if (bad)
         atomicOr(a.flags, bad);
     const uint32_t wvalid = wave_sum_u32(valid);
@@ -1116,8 +1111,8 @@ __global__ void __launch_bounds__(NT) trace_group_kernel(StatsArgs a)
     const uint32_t nvalid = s_valid;
     if (nvalid == 0)
         return;
-    mirror_sort_regs<E, NT>(k, s_buf, t);
-    group_sweep_regs<E, NT>(k, nvalid, base, s_sum, t);
+    mirror_sort_regs<FLOAT, E, NT>(k, s_buf, t);
+    group_sweep_regs<FLOAT, E, NT>(k, nvalid, s_sum, t);
     __syncthreads();
     unsigned long long *copy = a.totals + (uint64_t)(r % kStatsCopies) * kStatsCopyStride;
     if (t < 3 * M) {
@@ -1137,6 +1132,7 @@ __device__ __forceinline__ uint32_t sort_participants(const StatsArgs &a)
     return listed == 0 ? 1u : (listed < a.sort_grid ? listed : a.sort_grid);
 }
 
+template <bool FLOAT>
 __global__ void __launch_bounds__(kThreads) trace_sort_kernel(StatsArgs a)
 {
     extern __shared__ __align__(8) unsigned char s_dyn[];
@@ -1147,7 +1143,7 @@ __global__ void __launch_bounds__(kThreads) trace_sort_kernel(StatsArgs a)
     for (uint32_t w = blockIdx.x; w < listed; w += gridDim.x) {
         if (w != blockIdx.x)
             __syncthreads();                           // the previous trace's sums are read
-        one_trace<kSort>(a, a.work[w], 0, s_dyn);
+        one_trace<kSort, FLOAT>(a, a.work[w], 0, s_dyn);
     }
     finish_block(a, blockIdx.x, P + a.num_long);
 }
@@ -1158,6 +1154,39 @@ __global__ void __launch_bounds__(kThreads) trace_long_kernel(StatsArgs a)
     // the list is still intact here (no sort launch: its blocks have finished before)
     const uint32_t P = a.sort_grid ? sort_participants(a) : 0u;
     finish_block(a, P + blockIdx.x, P + a.num_long);
+}
+
+}  // namespace
+
+namespace {
+
+// The direct sort: every group size up to a.group_max, then the waves.
+template <bool FLOAT>
+hipError_t launch_direct(const StatsArgs &a, hipStream_t st)
+{
+    hipError_t e;
+    if (a.group_max > 1536) {
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(trace_group_kernel<FLOAT, 8, 256, 1536>), dim3(a.R),
+                           dim3(256), 0, st, a);
+        if ((e = hipGetLastError()) != hipSuccess)
+            return e;
+    }
+    if (a.group_max > 1024) {
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(trace_group_kernel<FLOAT, 8, 192, 1024>), dim3(a.R),
+                           dim3(192), 0, st, a);
+        if ((e = hipGetLastError()) != hipSuccess)
+            return e;
+    }
+    if (a.group_max > kWaveSortMax) {
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(trace_group_kernel<FLOAT, 8, 128, kWaveSortMax>),
+                           dim3(a.R), dim3(128), 0, st, a);
+        if ((e = hipGetLastError()) != hipSuccess)
+            return e;
+    }
+    hipLaunchKernelGGL(trace_wave_kernel<FLOAT>,
+                       dim3((a.R + kWaveSortWaves - 1) / kWaveSortWaves),
+                       dim3(64 * kWaveSortWaves), 0, st, a);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -1207,27 +1236,8 @@ hipError_t launch_trace_stats(const StatsLaunch &l, hipStream_t st)
         if ((e = hipGetLastError()) != hipSuccess)
             return e;
     } else if (l.order == kStatsDirect) {
-        if (a.group_max > 1536) {
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(trace_group_kernel<8, 256, 1536>), dim3(R),
-                               dim3(256), 0, st, a);
-            if ((e = hipGetLastError()) != hipSuccess)
-                return e;
-        }
-        if (a.group_max > 1024) {
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(trace_group_kernel<8, 192, 1024>), dim3(R),
-                               dim3(192), 0, st, a);
-            if ((e = hipGetLastError()) != hipSuccess)
-                return e;
-        }
-        if (a.group_max > kWaveSortMax) {
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(trace_group_kernel<8, 128, kWaveSortMax>),
-                               dim3(R), dim3(128), 0, st, a);
-            if ((e = hipGetLastError()) != hipSuccess)
-                return e;
-        }
-        hipLaunchKernelGGL(trace_wave_kernel, dim3((R + kWaveSortWaves - 1) / kWaveSortWaves),
-                           dim3(64 * kWaveSortWaves), 0, st, a);
-        if ((e = hipGetLastError()) != hipSuccess)
+        if ((e = a.M <= kFloatLlms ? launch_direct<true>(a, st) : launch_direct<false>(a, st)) !=
+            hipSuccess)
             return e;
     }
     a.sort_grid = 0;
@@ -1236,7 +1246,12 @@ hipError_t launch_trace_stats(const StatsLaunch &l, hipStream_t st)
         // blocks takes its entries in turn (an empty list costs one short launch).
         const size_t lds = (size_t)2 * l.lds_cap * sizeof(uint64_t);
         a.sort_grid = R > kSortBlocks ? kSortBlocks : R;
-        hipLaunchKernelGGL(trace_sort_kernel, dim3(a.sort_grid), dim3(kThreads), lds, st, a);
+        if (a.M <= kFloatLlms)
+            hipLaunchKernelGGL(trace_sort_kernel<true>, dim3(a.sort_grid), dim3(kThreads), lds, st,
+                               a);
+        else
+            hipLaunchKernelGGL(trace_sort_kernel<false>, dim3(a.sort_grid), dim3(kThreads), lds,
+                               st, a);
         if ((e = hipGetLastError()) != hipSuccess)
             return e;
     }

@@ -154,7 +154,7 @@ struct alp_ctx {
     DevBuf tables;                 // W | n | p | allowed | rate | lat
     alp::TablesDev tdev{};
 
-    DevBuf q_inst, rec, ext, inner, done, winners, idx, evals, tmax;   // q_inst: inst | cap | lambda
+    DevBuf q_inst, rec, ext, inner, done, winners, idx, evals;   // q_inst: inst | cap | lambda
     DevBuf pair;                            // pair tables of the scan's pair form
     DevBuf fused_regions;                   // one-launch scan: per-block option records
     DevBuf fused_words;                     // one-launch scan: per-item best word and counter,
@@ -1347,26 +1347,17 @@ int32_t alp_max_throughput(alp_ctx *ctx, uint32_t count, const uint32_t *instanc
     int32_t st = upload_queries(ctx, count, inst.data(), cap.data(), zero.data(), q);
     if (st != ALP_OK)
         return st;
+    // Results straight to mapped host memory (the search records' buffer).
+    if ((st = ensure_host_results(ctx, count)) != ALP_OK)
+        return st;
+    Marked mark("alp max_throughput");
     hipError_t e;
-    const size_t bytes = (size_t)count * sizeof(uint32_t);
-    const uint64_t items_bytes = (uint64_t)count * ctx->sp.M * ctx->sp.O * sizeof(uint2);
-    if ((e = ctx->tmax.ensure(bytes)) != hipSuccess || (e = ctx->rec.ensure(items_bytes)) != hipSuccess ||
-        (e = ctx->ext.ensure(items_bytes)) != hipSuccess)
-        return hip_fail(e, "hipMalloc(max_throughput)");
-    Marked mark("alp max_throughput: option terms and reduction");
-    if ((e = alp::launch_option_terms(ctx->sp, ctx->tdev, q, count, (uint2 *)ctx->rec.ptr,
-                                      (uint2 *)ctx->ext.ptr, nullptr, alp::ScanReset{}, ctx->stream)) !=
-        hipSuccess)
-        return hip_fail(e, "option_terms launch");
-    if ((e = alp::launch_tmax(ctx->sp, q, count, (const uint2 *)ctx->ext.ptr,
-                              (uint32_t *)ctx->tmax.ptr, ctx->stream)) != hipSuccess)
+    if ((e = alp::launch_tmax(ctx->sp, ctx->tdev, q, count, (uint32_t *)ctx->host_results_dev,
+                              ctx->stream)) != hipSuccess)
         return hip_fail(e, "tmax launch");
-    std::vector<uint32_t> host(count);
-    if ((e = hipMemcpyAsync(host.data(), ctx->tmax.ptr, bytes, hipMemcpyDeviceToHost, ctx->stream)) != hipSuccess)
-        return hip_fail(e, "copy results");
     if ((e = hipStreamSynchronize(ctx->stream)) != hipSuccess)
         return hip_fail(e, "hipStreamSynchronize");
-    memcpy(out_tmax, host.data(), bytes);
+    memcpy(out_tmax, ctx->host_results, (size_t)count * sizeof(uint32_t));
     return ALP_OK;
 }
 
@@ -1807,7 +1798,7 @@ void alp_free(alp_ctx *ctx)
             for (hipEvent_t x : t)
                 (void)hipEventDestroy(x);
     DevBuf *bufs[] = {&ctx->tables, &ctx->q_inst, &ctx->rec, &ctx->ext, &ctx->inner, &ctx->done,
-                      &ctx->winners, &ctx->idx, &ctx->evals, &ctx->tmax, &ctx->split_dp,
+                      &ctx->winners, &ctx->idx, &ctx->evals, &ctx->split_dp,
                       &ctx->pruned_table,
                       &ctx->place_in, &ctx->place_out, &ctx->pair, &ctx->fused_regions,
                       &ctx->fused_words};

@@ -464,12 +464,23 @@ struct CurveLds {
     }
 };
 
+// tau = floor(1000 d T / n), saturated at 2^32 - 1, with inv_n = recip_low<2, 50>(n): the quotient
+// is below 2^45 and the estimate below it by less than 1.3 * 2^-50 * 2^45 < 2^-4, so an estimate at
+// or above 2^32 saturates, below it is the quotient or one less, and a quotient of 2^32 saturates
+// too.  dd = 1000 d; dd T is exact in a double.
+__device__ __forceinline__ uint32_t option_tau(uint32_t dd, uint32_t T, uint32_t n, double inv_n)
+{
+    const uint64_t dT = (uint64_t)dd * T;
+    const double tau_est = ((double)dd * (double)T) * inv_n;
+    const uint32_t tq = (uint32_t)fmin(tau_est, 4294967295.0);
+    const bool tau_up = (uint32_t)dT - tq * n >= n && tq != 0xFFFFFFFFu;
+    return tau_est >= 4294967296.0 ? 0xFFFFFFFFu : tq + (tau_up ? 1u : 0u);
+}
+
 // The terms of an option with d replicas of its LLM, from the LLM's profile curve for the
 // option's (tp, share) pair, whether that curve is deployable, tpq = tp * q, the LLM's inputs,
 // the target lambda and inv_dd = recip_low<1, 40>(1000 d).  Every quotient is one udiv_low:
-//   * tau < 2^45 with the <2, 50> reciprocal of n (an estimate below the quotient by less than
-//     1.3 * 2^-50 * 2^45 < 2^-4): an estimate at or above 2^32 saturates, below it is the
-//     quotient or one less, and a quotient of 2^32 saturates too;
+//   * tau is option_tau();
 //   * thr is lambda n <= 1000 d T (for an integer T, ceil(y) <= T iff y <= T), a product test;
 //     with thr, r <= T < 2^31 and lambda n + 1000 d - 1 < 2^46 is an exact double;
 //   * ell < 2^31 lies between two latencies;
@@ -490,10 +501,7 @@ __device__ __forceinline__ OptionTerm option_term_core(uint32_t d, const Curve &
     const uint32_t T = cv.last_rate();
     const uint64_t dT = (uint64_t)dd * T;
     const double n_f = (double)l.n;
-    const double tau_est = ((double)dd * (double)T) * l.inv_n;      // dT exact in a double
-    const uint32_t tq = (uint32_t)fmin(tau_est, 4294967295.0);
-    const bool tau_up = (uint32_t)dT - tq * l.n >= l.n && tq != 0xFFFFFFFFu;
-    t.tau = tau_est >= 4294967296.0 ? 0xFFFFFFFFu : tq + (tau_up ? 1u : 0u);
+    t.tau = option_tau(dd, T, l.n, l.inv_n);
     const uint64_t load = (uint64_t)lambda * l.n;
     t.thr = load <= dT;
     const uint32_t r = udiv_low(fma((double)lambda, n_f, (double)(dd - 1)),

@@ -255,7 +255,7 @@ hipError_t launch_packed(const SpaceDev &sp, const QueryDev &q, uint32_t count,
                          hipStream_t st, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
 hipError_t launch_eval(const SpaceDev &sp, uint32_t capacity, const uint2 *rec, const uint2 *ext,
                        const uint64_t *idx, uint64_t count, alp_eval_t *out, hipStream_t st);
-hipError_t launch_tmax(const SpaceDev &sp, const QueryDev &q, uint32_t count, const uint2 *ext,
+hipError_t launch_tmax(const SpaceDev &sp, const TablesDev &tb, const QueryDev &q, uint32_t count,
                        uint32_t *out, hipStream_t st);
 
 // Budget split over W workflows from their per-budget search results (res[w * (G + 1) + g]),

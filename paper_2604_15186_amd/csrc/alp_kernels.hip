@@ -1189,141 +1189,98 @@ eval_kernel(SpaceDev sp, uint32_t capacity, const uint2 *__restrict__ rec,
 }
 
 // ---------------------------------------------------------------------------------------------
-// Largest reachable T_w within the budget, one block per item.  T_w >= t is reachable iff the
-// cheapest deployable, fitting options with tau >= t of all LLMs together fit:
-// need(t) = sum_m min{u : ok, tau >= t} <= capacity.  The maximum is one of the options' own
-// taus.  Per LLM, the deployable options are ranked by tau descending (ties by option index)
-// and a running minimum of their units is taken along that order; need(t) for each candidate
-// t then costs one binary search per LLM.  O(M * O * (O + M log O)) work per item, in LDS; one
-// thread per option where the block allows.
-constexpr uint32_t kTmaxStride = 8;     // options per LLM padded to this (whole 16-byte reads)
+// Largest reachable T_w within the budget, one wave per item, a few items per block.  T_w >= t is
+// reachable iff the cheapest deployable, fitting options with tau >= t of all LLMs together fit:
+// need(t) = sum_m min{u : tau >= t} <= capacity.  That is monotone in t and the largest such t is
+// one of the taus, so it is found bit by bit below min_m max tau, each step a pass over the
+// options in LDS and a minimum per LLM over the wave (two LLMs to a register: units are at most
+// 64 * 16 * 16).  What bounds it: latency, some 20 steps of an LDS round trip and 12 cross-lane
+// moves, hidden by the other items' waves.  The wave computes the taus itself from the curves'
+// last points: 4,096 3-LLM items take one launch and 38.5 us per call, against 80.7 us with 17 us
+// of kernel for their option terms and 32 us for ranking every LLM's options (O^2 compares).
+constexpr uint32_t kNoUnits = 0x7FFFu;
+constexpr uint32_t kTmaxWaves = 4;
+constexpr size_t kTmaxLds = 48 * 1024;
 
-__host__ __device__ inline uint32_t tmax_stride(uint32_t O)
+template <int M>
+__global__ void __launch_bounds__(64 * kTmaxWaves)
+tmax_kernel(SpaceDev sp, TablesDev tb, QueryDev q, uint32_t count, uint32_t mul_fq,
+            uint32_t *__restrict__ out)
 {
-    return (O + kTmaxStride - 1) / kTmaxStride * kTmaxStride;
-}
-
-__global__ void __launch_bounds__(1024)
-tmax_kernel(SpaceDev sp, QueryDev q, const uint2 *__restrict__ ext, uint32_t *__restrict__ out)
-{
-    extern __shared__ uint4 t_lds4[];
-    constexpr uint16_t kUnusable = 0xFFFFu;   // share units are at most 64 * 16 * 16 = 16384
-    constexpr uint64_t kNoKey = ~0ull;        // not deployable (or padding): ranks last
-    const uint32_t item = blockIdx.x;
-    const uint32_t O = sp.O, MO = sp.M * O, P = tmax_stride(O), MP = sp.M * P;
-    // Each option's rank key: (2^32 - 1 - tau) << 32 | index, so that ascending keys are tau
-    // descending then index ascending, and one 64-bit compare orders two options.
-    uint64_t *key = reinterpret_cast<uint64_t *>(t_lds4);   // [M][P]
-    uint32_t *stau = reinterpret_cast<uint32_t *>(key + MP); // [M][P] deployable taus, descending
-    uint16_t *units = (uint16_t *)(stau + MP);           // [M][P] share units, or kUnusable
-    uint16_t *smin = units + MP;                         // [M][P] running minimum of units
-    __shared__ uint32_t s_count[ALP_MAX_LLMS];
-    __shared__ uint32_t s_best[16];
-    const uint2 *E = ext + (uint64_t)item * MO;
-    if (threadIdx.x < ALP_MAX_LLMS)
-        s_count[threadIdx.x] = 0;
-    for (uint32_t a = threadIdx.x; a < MP; a += blockDim.x) {
-        const uint32_t m = a / P, o = a - m * P;
-        uint2 e = make_uint2(0u, 0u);                    // padding: not deployable
-        if (o < O)
-            e = E[m * O + o];
-        const bool usable = (e.y >> 16) & 1u;
-        key[a] = usable ? (uint64_t)(0xFFFFFFFFu - e.x) << 32 | o : kNoKey;
-        units[a] = usable ? (uint16_t)(e.y & 0xFFFFu) : kUnusable;
+    extern __shared__ uint2 s_opt[];
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t item = blockIdx.x * (blockDim.x >> 6) + wave;
+    if (item >= count)
+        return;                                    // (no barrier below: waves are independent)
+    uint2 *opt = s_opt + wave * M * sp.O;          // (tau, 0 if not deployable; share units)
+    uint32_t inst, cap, lambda;
+    load_query(q, item, inst, cap, lambda);
+    const uint64_t lm0 = (uint64_t)inst * M;
+    const uint32_t pairs = sp.n_tp * sp.n_fq, curves = M * pairs;
+    // A curve per lane at a time: its last rate and deployability, then its D options.
+    for (uint32_t c = lane; c < curves; c += 64) {
+        const uint32_t m = c / pairs, ij = c - m * pairs, i = div_by(ij, mul_fq);
+        const uint64_t tab = lm0 * pairs + c;
+        const uint32_t T = tb.rate[tab * sp.K + sp.K - 1], n = tb.n[lm0 + m];
+        const uint32_t tpq = sp.tp(i) * sp.fq(ij - i * sp.n_fq);
+        const bool ok = deployable(sp, tb.H, tb.allowed[tab] != 0, tb.W[lm0 + m], tpq);
+        const double inv_n = recip_low<2, 50>(n);
+        for (uint32_t d = 1; d <= sp.D; ++d)
+            opt[c * sp.D + d - 1] =
+                make_uint2(ok ? option_tau(1000u * d, T, n, inv_n) : 0u, tpq * d);
     }
-    __syncthreads();
-    // Rank of each deployable option within its LLM: the keys of the LLM below its own, read
-    // two at a time (a compare and an add each).
-    for (uint32_t a = threadIdx.x; a < MP; a += blockDim.x) {
-        const uint64_t mine = key[a];
-        if (mine == kNoKey)
-            continue;
-        const uint32_t m = a / P;
-        const uint4 *K2 = reinterpret_cast<const uint4 *>(key + m * P);
-        uint32_t rank = 0;
-#pragma unroll 4
-        for (uint32_t j2 = 0; j2 < P / 2; ++j2) {
-            const uint4 kk = K2[j2];
-            rank += ((uint64_t)kk.y << 32 | kk.x) < mine;
-            rank += ((uint64_t)kk.w << 32 | kk.z) < mine;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    uint32_t top = 0xFFFFFFFFu;
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        uint32_t t = 0;
+        for (uint32_t o = lane; o < sp.O; o += 64) {
+            const uint32_t tau = opt[m * sp.O + o].x;
+            t = tau > t ? tau : t;
         }
-        stau[m * P + rank] = 0xFFFFFFFFu - (uint32_t)(mine >> 32);
-        smin[m * P + rank] = units[a];
-        atomicAdd(&s_count[m], 1u);
+        t = wave_max_u32(t);
+        top = t < top ? t : top;
     }
-    __syncthreads();
-    // Running minimum along each LLM's order: wave w takes LLMs w, w + waves, ...; lane l holds
-    // a contiguous run of the order, minimum within the run, then a prefix minimum of the runs
-    // across the lanes.
-    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    for (uint32_t m = wave; m < sp.M; m += nw) {
-        const uint32_t n = s_count[m], per = (n + 63) / 64;
-        uint16_t *S = smin + m * P;
-        const uint32_t lo = lane * per, hi = lo + per < n ? lo + per : n;
-        uint32_t run = 0xFFFFFFFFu;
-        for (uint32_t k = lo; k < hi; ++k)
-            run = S[k] < run ? S[k] : run;
-        // Inclusive prefix minimum over the lanes by DPP (row shifts by 1, 2, 4, 8, then lane
-        // 15 into rows 1 and 3 and lane 31 into rows 2 and 3; lanes a move does not reach keep
-        // the identity), then the exclusive one by a shift of the whole wave.
-        uint32_t before = run;
-        auto step = [&](auto c, auto rm) {
-            constexpr int C = decltype(c)::value, RM = decltype(rm)::value;
-            const uint32_t o = dpp_mov<C, RM>(0xFFFFFFFFu, before);
-            before = o < before ? o : before;
-        };
-        step(std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xF>{});
-        step(std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xF>{});
-        step(std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xF>{});
-        step(std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xF>{});
-        step(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xA>{});
-        step(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xC>{});
-        uint32_t acc = dpp_mov<0x138>(0xFFFFFFFFu, before);
-        for (uint32_t k = lo; k < hi; ++k) {
-            acc = S[k] < acc ? S[k] : acc;
-            S[k] = (uint16_t)acc;
-        }
-    }
-    __syncthreads();
-    const uint64_t capacity = (uint64_t)query_value(q.capacity, q.cap1, item);
+    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
     uint32_t best = 0;
-    for (uint32_t a = threadIdx.x; a < MP; a += blockDim.x) {
-        if (key[a] == kNoKey)
+    for (uint32_t bit = top ? 0x80000000u >> __builtin_clz(top) : 0u; bit; bit >>= 1) {
+        const uint32_t t = best | bit;
+        if (t > top)
             continue;
-        const uint32_t t = 0xFFFFFFFFu - (uint32_t)(key[a] >> 32);
-        if (t <= best)
-            continue;
-        uint64_t need = 0;
-        bool reachable = true;
-        for (uint32_t m = 0; m < sp.M && reachable; ++m) {
-            // options of m with tau >= t: the first c of its descending order
-            uint32_t lo = 0, hi = s_count[m];
-            const uint32_t *S = stau + m * P;
-            while (lo < hi) {
-                const uint32_t mid = (lo + hi) >> 1;
-                if (S[mid] >= t)
-                    lo = mid + 1;
-                else
-                    hi = mid;
+        uint32_t units[(M + 1) / 2 * 2];
+#pragma unroll
+        for (int m = 0; m < (M + 1) / 2 * 2; ++m)
+            units[m] = m < M ? kNoUnits : 0u;
+        for (uint32_t o = lane; o < sp.O; o += 64) {
+#pragma unroll
+            for (int m = 0; m < M; ++m) {
+                const uint2 v = opt[m * sp.O + o];
+                const uint32_t u = v.x >= t ? v.y : kNoUnits;
+                units[m] = u < units[m] ? u : units[m];
             }
-            if (lo == 0)
-                reachable = false;
-            else
-                need += smin[m * P + lo - 1];
         }
-        if (reachable && need <= capacity)
-            best = t;
+        uint32_t need = 0;
+        bool some = true;
+#pragma unroll
+        for (int h = 0; h < (M + 1) / 2; ++h) {
+            uint32_t v = units[2 * h] | (units[2 * h + 1] << 16);
+            wave_reduce_steps([&](auto c, auto rm) {
+                constexpr int C = decltype(c)::value, RM = decltype(rm)::value;
+                const uint32_t o = dpp_mov<C, RM>(v, v);
+                v = __builtin_bit_cast(uint32_t,
+                                       __builtin_elementwise_min(__builtin_bit_cast(u16x2, v),
+                                                                 __builtin_bit_cast(u16x2, o)));
+            });
+            v = lane63(v);
+            some = some && (v & 0xFFFFu) != kNoUnits && (v >> 16) != kNoUnits;
+            need += (v & 0xFFFFu) + (v >> 16);
+        }
+        best = some && need <= cap ? t : best;
     }
-    best = wave_max_u32(best);
     if (lane == 0)
-        s_best[wave] = best;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t b = 0;
-        for (uint32_t w = 0; w < nw; ++w)
-            b = s_best[w] > b ? s_best[w] : b;
-        out[item] = b;
-    }
+        out[item] = best;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1471,16 +1428,34 @@ hipError_t launch_eval(const SpaceDev &sp, uint32_t capacity, const uint2 *rec, 
     return hipGetLastError();
 }
 
-hipError_t launch_tmax(const SpaceDev &sp, const QueryDev &q, uint32_t count, const uint2 *ext,
+hipError_t launch_tmax(const SpaceDev &sp, const TablesDev &tb, const QueryDev &q, uint32_t count,
                        uint32_t *out, hipStream_t st)
 {
     if (count == 0)
         return hipSuccess;
-    const uint32_t MP = sp.M * tmax_stride(sp.O);
-    const size_t lds = (size_t)MP * (sizeof(uint64_t) + sizeof(uint32_t) + 2 * sizeof(uint16_t));
-    // one thread per option (padded), in whole waves, 64..1024
-    const uint32_t threads = MP >= 1024 ? 1024u : (MP + 63) / 64 * 64;
-    hipLaunchKernelGGL(tmax_kernel, dim3(count), dim3(threads), lds, st, sp, q, ext, out);
+    const size_t per_wave = (size_t)sp.M * sp.O * sizeof(uint2);      // at most 32 KiB
+    const uint32_t waves =
+        (uint32_t)(kTmaxLds / per_wave < kTmaxWaves ? kTmaxLds / per_wave : kTmaxWaves);
+    const uint32_t mul_fq = div_multiplier(sp.n_fq);
+    const dim3 grid((count + waves - 1) / waves), block(64 * waves);
+#define ALP_TMAX_CASE(MM)                                                                          \
+    case MM:                                                                                       \
+        hipLaunchKernelGGL(tmax_kernel<MM>, grid, block, waves * per_wave, st, sp, tb, q, count,   \
+                           mul_fq, out);                                                           \
+        break;
+    switch (sp.M) {
+        ALP_TMAX_CASE(1)
+        ALP_TMAX_CASE(2)
+        ALP_TMAX_CASE(3)
+        ALP_TMAX_CASE(4)
+        ALP_TMAX_CASE(5)
+        ALP_TMAX_CASE(6)
+        ALP_TMAX_CASE(7)
+        ALP_TMAX_CASE(8)
+    default:
+        return hipErrorInvalidValue;
+    }
+#undef ALP_TMAX_CASE
     return hipGetLastError();
 }
 

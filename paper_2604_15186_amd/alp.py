@@ -283,7 +283,7 @@ class Context:
         res = np.ascontiguousarray(allocations, dtype=RESULT_DTYPE)
         G = np.ascontiguousarray(gpu_budget, dtype=np.uint32)
         assert len(G) == len(res)
-        out = np.zeros(len(res), dtype=PLACEMENT_DTYPE)
+        out = np.empty(len(res), dtype=PLACEMENT_DTYPE)     # every byte is written
         _check(lib().alp_place(self._ctx, len(res), _ptr(res), _ptr(G), _ptr(out)))
         return out
 

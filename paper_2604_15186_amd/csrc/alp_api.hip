@@ -13,6 +13,7 @@
 #include <array>
 #include <chrono>
 #include <cmath>
+#include <memory>
 #include <new>
 #include <vector>
 
@@ -162,6 +163,8 @@ struct alp_ctx {
     DevBuf split_dp;                        // allocate_kernel's knapsack table
     DevBuf pruned_table;                    // pruned search: option tables too large for LDS
     DevBuf place_in, place_out;                          // placement records
+    std::unique_ptr<uint8_t[]> host_place;               // their host side
+    size_t host_place_cap = 0;                           // bytes
     alp_pruned_t *host_pruned = nullptr;    // mapped pinned results of pruned searches
     alp_pruned_t *host_pruned_dev = nullptr;
     size_t host_pruned_cap = 0;
@@ -1583,8 +1586,32 @@ int32_t alp_place(alp_ctx *ctx, uint32_t count, const alp_result_t *allocations,
     if (!allocations || !gpu_budget || !out)
         return fail(ALP_EINVAL, "allocations, gpu_budget or out is NULL");
     const alp_space_t &sp = ctx->space;
+    // A record holds slots for every replica that the space allows; the rest of
+    // alp_placement_t's 128 are "not placed" and are filled in here, not copied (4,096 3-LLM
+    // allocations of up to 8 replicas an LLM: 64 bytes each instead of 272).
+    // What bounds the call is host memory and the copies, not the 13 us kernel: 161 us with whole
+    // records copied into fresh pages and choices checked by search, 85 now.  Writing whole records
+    // to mapped host memory took 101 and 560 us more on a context's first call (pinning).
+    const uint32_t slots = (sp.num_llms * sp.max_replicas + 7u) & ~7u;
+    const size_t stride = offsetof(alp_placement_t, slot) + slots * sizeof(uint16_t);
+    const size_t in_bytes = count * sizeof(alp::PlaceIn), out_bytes = count * stride;
+    if (in_bytes + out_bytes > ctx->host_place_cap) {
+        ctx->host_place_cap = 0;
+        ctx->host_place.reset(new (std::nothrow) uint8_t[in_bytes + out_bytes]);
+        if (!ctx->host_place)
+            return hip_fail(hipErrorOutOfMemory, "placement records");
+        ctx->host_place_cap = in_bytes + out_bytes;
+    }
+    alp::PlaceIn *in = reinterpret_cast<alp::PlaceIn *>(ctx->host_place.get());
+    uint8_t *packed = ctx->host_place.get() + in_bytes;
+    bool tp_ok[256] = {}, q_ok[256] = {};
+    for (uint32_t j = 0; j < sp.num_tp; ++j)
+        if (sp.tp_values[j] <= ALP_NODE_GPUS)
+            tp_ok[sp.tp_values[j]] = true;
+    for (uint32_t j = 0; j < sp.num_frac; ++j)
+        if (sp.frac_units[j] <= 255)
+            q_ok[sp.frac_units[j]] = true;
     // Budgets of at most 16 GPUs first (four to a wave), then the others.
-    std::vector<alp::PlaceIn> in(count);
     uint32_t small = 0;
     for (uint32_t i = 0; i < count; ++i)
         small += gpu_budget[i] <= 16;
@@ -1595,53 +1622,52 @@ int32_t alp_place(alp_ctx *ctx, uint32_t count, const alp_result_t *allocations,
             return fail(ALP_EINVAL, "allocation %u: %u GPUs, at most %u", i, gpu_budget[i],
                         ALP_PLACE_MAX_GPUS);
         alp::PlaceIn &p = in[gpu_budget[i] <= 16 ? next_small++ : next_large++];
-        memset(&p, 0, sizeof(p));
-        p.dst = i;
-        p.gpus = (uint8_t)gpu_budget[i];
-        p.llms = (uint8_t)sp.num_llms;
-        p.feasible = r.status == ALP_OK;
-        if (!p.feasible)
-            continue;
-        for (uint32_t m = 0; m < sp.num_llms; ++m) {
-            bool tp_ok = false, q_ok = false;
-            for (uint32_t j = 0; j < sp.num_tp; ++j)
-                tp_ok |= r.tp[m] == sp.tp_values[j];
-            for (uint32_t j = 0; j < sp.num_frac; ++j)
-                q_ok |= r.frac_units[m] == sp.frac_units[j];
-            if (!tp_ok || !q_ok || r.tp[m] > ALP_NODE_GPUS || r.replicas[m] < 1 ||
+        alp::PlaceIn v{};
+        v.dst = i;
+        v.gpus = (uint8_t)gpu_budget[i];
+        v.llms = (uint8_t)sp.num_llms;
+        v.feasible = r.status == ALP_OK;
+        for (uint32_t m = 0; v.feasible && m < sp.num_llms; ++m) {
+            if (!tp_ok[r.tp[m]] || !q_ok[r.frac_units[m]] || r.replicas[m] < 1 ||
                 r.replicas[m] > sp.max_replicas)
                 return fail(ALP_EINVAL, "allocation %u: LLM %u's choice is not of the space", i, m);
-            p.tp[m] = r.tp[m];
-            p.q[m] = r.frac_units[m];
-            p.d[m] = r.replicas[m];
+            v.tp[m] = r.tp[m];
+            v.q[m] = r.frac_units[m];
+            v.d[m] = r.replicas[m];
         }
+        p = v;
     }
     DeviceGuard guard(ctx->device);
     if (guard.status != hipSuccess)
         return hip_fail(guard.status, "hipSetDevice");
     begin_call(ctx);
     hipError_t e;
-    if ((e = ctx->place_in.ensure(count * sizeof(alp::PlaceIn))) != hipSuccess ||
-        (e = ctx->place_out.ensure(count * sizeof(alp_placement_t))) != hipSuccess)
+    if ((e = ctx->place_in.ensure(in_bytes)) != hipSuccess ||
+        (e = ctx->place_out.ensure(out_bytes)) != hipSuccess)
         return hip_fail(e, "hipMalloc(placement)");
     if (ctx->timing && (e = hipEventRecord(ctx->ev[0], ctx->stream)) != hipSuccess)
         return hip_fail(e, "hipEventRecord");
-    if ((e = hipMemcpyAsync(ctx->place_in.ptr, in.data(), count * sizeof(alp::PlaceIn),
-                            hipMemcpyHostToDevice, ctx->stream)) != hipSuccess)
+    if ((e = hipMemcpyAsync(ctx->place_in.ptr, in, in_bytes, hipMemcpyHostToDevice,
+                            ctx->stream)) != hipSuccess)
         return hip_fail(e, "copy allocations");
     if (ctx->timing && (e = hipEventRecord(ctx->ev[1], ctx->stream)) != hipSuccess)
         return hip_fail(e, "hipEventRecord");
     Marked mark("alp place");
-    if ((e = alp::launch_place(sp.units_per_gpu, small, count - small,
+    if ((e = alp::launch_place(sp.units_per_gpu, slots, small, count - small,
                                (const alp::PlaceIn *)ctx->place_in.ptr,
-                               (alp_placement_t *)ctx->place_out.ptr, ctx->stream)) != hipSuccess)
+                               (uint32_t *)ctx->place_out.ptr, ctx->stream)) != hipSuccess)
         return hip_fail(e, "placement launch");
     if (ctx->timing && (e = hipEventRecord(ctx->ev[2], ctx->stream)) != hipSuccess)
         return hip_fail(e, "hipEventRecord");
-    if ((e = hipMemcpyAsync(out, ctx->place_out.ptr, count * sizeof(alp_placement_t),
-                            hipMemcpyDeviceToHost, ctx->stream)) != hipSuccess ||
+    if ((e = hipMemcpyAsync(packed, ctx->place_out.ptr, out_bytes, hipMemcpyDeviceToHost,
+                            ctx->stream)) != hipSuccess ||
         (e = hipStreamSynchronize(ctx->stream)) != hipSuccess)
         return hip_fail(e, "placement");
+    for (uint32_t i = 0; i < count; ++i) {
+        uint8_t *rec = reinterpret_cast<uint8_t *>(out + i);
+        memcpy(rec, packed + i * stride, stride);
+        memset(rec + stride, 0xFF, sizeof(alp_placement_t) - stride);
+    }
     if (ctx->timing) {
         // ms[1]: the placement kernel
         if ((e = hipEventElapsedTime(&ctx->last_ms[1], ctx->ev[1], ctx->ev[2])) != hipSuccess)

@@ -343,9 +343,10 @@ struct PlaceIn {
 
 // Placement (see alp_place); Q share units per GPU.  in[0..small) have budgets of at most 16
 // GPUs (placed four to a wave), in[small..small + large) the others (one to a wave); each
-// writes out[in[i].dst].
-hipError_t launch_place(uint32_t Q, uint32_t small, uint32_t large, const PlaceIn *in,
-                        alp_placement_t *out, hipStream_t st);
+// writes record in[i].dst of out: an alp_placement_t cut to its first `slots` slots (a multiple of
+// 8, at least every allocation's replicas).
+hipError_t launch_place(uint32_t Q, uint32_t slots, uint32_t small, uint32_t large,
+                        const PlaceIn *in, uint32_t *out, hipStream_t st);
 
 static_assert(sizeof(alp_placement_t) == 272 && offsetof(alp_placement_t, slot) == 16,
               "alp_placement_t layout");

@@ -105,8 +105,8 @@ __device__ __forceinline__ uint32_t group_read(uint32_t v, uint32_t src)
 // depends only on the allocation, so its lanes take the same path.
 template <uint32_t L>
 __global__ void __launch_bounds__(64 * kWavesPerBlock)
-place_kernel(uint32_t Q, uint32_t count, const PlaceIn *__restrict__ in,
-             alp_placement_t *__restrict__ out)
+place_kernel(uint32_t Q, uint32_t num_slots, uint32_t count, const PlaceIn *__restrict__ in,
+             uint32_t *__restrict__ out)
 {
     constexpr uint32_t kPerWave = 64 / L, kWords = 64 / L;   // allocations, slot words per lane
     const uint32_t lane = threadIdx.x & 63;
@@ -261,39 +261,43 @@ place_kernel(uint32_t Q, uint32_t count, const PlaceIn *__restrict__ in,
             ++done;
         }
     }
-    alp_placement_t *dst = out + a.dst;
+    // The record: alp_placement_t's four fields, then the slots that the space can use.  (Whole
+    // lanes: num_slots is a multiple of 8, a lane's are 2 or 8.)
+    uint32_t *dst = out + (size_t)a.dst * (4 + num_slots / 2);
+    if (gl * 2 * kWords < num_slots) {
 #pragma unroll
-    for (uint32_t kk = 0; kk < kWords; ++kk)
-        reinterpret_cast<uint32_t *>(dst->slot)[gl * kWords + kk] = slots[kk];
+        for (uint32_t kk = 0; kk < kWords; ++kk)
+            dst[4 + gl * kWords + kk] = slots[kk];
+    }
     const uint64_t used_all = __ballot(gpu && F.get(pos) < Q) >> first_lane;
     const uint64_t used = L == 64 ? used_all : used_all & ((1ull << L) - 1);
     uint32_t used_nodes = 0;
     for (uint32_t n = 0; n < L / kNode; ++n)
         used_nodes += (used >> (n * kNode) & 0xFFu) != 0;
     if (gl == 0) {
-        dst->status = placed ? ALP_OK : ALP_INFEASIBLE;
-        dst->replicas = done;
-        dst->gpus_used = (uint32_t)__popcll(used);
-        dst->nodes_used = used_nodes;
+        dst[0] = placed ? ALP_OK : ALP_INFEASIBLE;     // status, replicas, gpus_used, nodes_used
+        dst[1] = done;
+        dst[2] = (uint32_t)__popcll(used);
+        dst[3] = used_nodes;
     }
 }
 
 }  // namespace
 
-hipError_t launch_place(uint32_t Q, uint32_t small, uint32_t large, const PlaceIn *in,
-                        alp_placement_t *out, hipStream_t st)
+hipError_t launch_place(uint32_t Q, uint32_t slots, uint32_t small, uint32_t large,
+                        const PlaceIn *in, uint32_t *out, hipStream_t st)
 {
     if (small) {
         const uint32_t per_block = kWavesPerBlock * 4;
         hipLaunchKernelGGL(place_kernel<16>, dim3((small + per_block - 1) / per_block),
-                           dim3(64 * kWavesPerBlock), 0, st, Q, small, in, out);
+                           dim3(64 * kWavesPerBlock), 0, st, Q, slots, small, in, out);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return e;
     }
     if (large) {
         hipLaunchKernelGGL(place_kernel<64>, dim3((large + kWavesPerBlock - 1) / kWavesPerBlock),
-                           dim3(64 * kWavesPerBlock), 0, st, Q, large, in + small, out);
+                           dim3(64 * kWavesPerBlock), 0, st, Q, slots, large, in + small, out);
         return hipGetLastError();
     }
     return hipSuccess;

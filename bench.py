@@ -64,8 +64,11 @@ sys.path.insert(0, ROOT)
 from workloads import CONFIGS, make_batch, make_custom, target_from_tmax  # noqa: E402
 
 MI355X_CUS, MI355X_CLOCK_HZ = 256, 2.4e9    # published figures, used if rocminfo cannot be read
-OPS_PER_CANDIDATE = 2                   # budget compare + objective min: the work issued
-FRAC_BASIS = "issued VALU lane-ops (2 per candidate: budget compare, objective minimum)"
+# The packed scan issues 5 lane-operations per 4 candidates: a packed subtraction and a packed
+# maximum per record and pair of lane options, one three-operand packed minimum per two records.
+OPS_PER_CANDIDATE = 1.25
+FRAC_BASIS = ("issued VALU lane-ops (1.25 per candidate: packed budget subtraction, maximum and "
+              "three-operand minimum)")
 # Kernel times come from a separate pass after the timed region, every step event-stamped (an
 # event-stamped dispatch costs the GPU a few microseconds of idle time, which must not be part
 # of the timed steps of a small search); the figure reported is the median.
@@ -73,7 +76,7 @@ TIMING_SAMPLES = 9
 # The wider count of lane-ops per candidate (add the last term, compare the budget, compare the
 # best, select value and index), reported beside ``frac`` for comparison with that accounting.
 OPS_PER_CANDIDATE_WIDE = 5
-SQ_COUNTER_FILE = os.path.join(ROOT, "profiles", "scan_min_sq_counters.md")
+SQ_COUNTER_FILE = os.path.join(ROOT, "profiles", "scan_packed_sq_counters.md")
 # Exhaustive workloads measured besides the headline one in the default run.
 OTHER_WORKLOADS = ("cfg2", "cfg4", "cfg1", "cfg0")
 WORKLOADS = {"cfg0": 0, "cfg2": 2, "cfg3": 3, "cfg4": 4, "cfg1": 1, "multi": 2, "pruned": 4,
@@ -83,8 +86,8 @@ STATS_TRACES = 20_000                   # beam-search requests of the statistics
 # Several workflows sharing one GPU pool: four 4-LLM workflows drawn like the 4-LLM workload
 # split 32 GPUs under egalitarian welfare; each workflow's target is set at an even share.
 MULTI_WORKFLOWS, MULTI_GPUS = 4, 32
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "scan_min_hbm_bytes.md")
-KERNEL_SOURCES = ("alp_kernels.hip", "alp_device.h", "alp_internal.h")
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "scan_packed_hbm_bytes.md")
+KERNEL_SOURCES = ("alp_packed.hip", "alp_kernels.hip", "alp_device.h", "alp_internal.h")
 STATS_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "trace_stats_hbm_bytes.md")
 STATS_SOURCES = ("alp_stats.hip", "alp_device.h", "alp_internal.h")
 METRIC = "ALP candidate allocations evaluated/sec on 1 GPU"

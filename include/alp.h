@@ -305,10 +305,21 @@ int32_t alp_stats_create(alp_stats_ctx **out, int32_t device, void *hip_stream);
  * under 2^32 us take the fast path (no sort).  A context whose call finds most traces out of
  * end order sorts every trace directly from its next call on, until it finds most in order.  The
  * context's scratch grows to 4 bytes per trace plus, for traces beyond 2,048 calls, 16 bytes
- * per call rounded up to a power of two per trace. */
+ * per call rounded up to a power of two per trace.  Malformed offsets are refused before a call is
+ * read: the offsets are copied to the host and checked there first. */
 int32_t alp_trace_stats(alp_stats_ctx *ctx, uint32_t num_llms, uint32_t num_traces,
                         const uint64_t *offsets, const uint32_t *llm, const uint64_t *start_us,
                         const uint64_t *end_us, alp_stats_t *out);
+
+/* alp_trace_stats for a caller that knows how many entries the three call arrays hold: num_calls,
+ * EINVAL if offsets[num_traces] exceeds it.  The kernels check every trace's offsets against it
+ * before they read a call, so that malformed offsets cannot lead beyond the arrays, and the call
+ * needs no copy of the offsets to the host (unless they are malformed, an array is NULL, or there
+ * are traces beyond 2,048 calls). */
+int32_t alp_trace_stats_sized(alp_stats_ctx *ctx, uint32_t num_llms, uint32_t num_traces,
+                              const uint64_t *offsets, const uint32_t *llm,
+                              const uint64_t *start_us, const uint64_t *end_us,
+                              uint64_t num_calls, alp_stats_t *out);
 
 /* Enables HIP-event timing; alp_stats_time gives the milliseconds of the last computation's
  * kernels (initialisation to final division). */

@@ -23,7 +23,8 @@ MAX_LLMS = 8
 EXPORTS = ("alp_load_profiles", "alp_search", "alp_search_batch", "alp_search_batch_async",
            "alp_search_batch_async_noalloc",
            "alp_max_throughput", "alp_allocate_workflows", "alp_search_pruned", "alp_stats_create",
-           "alp_trace_stats", "alp_stats_set_timing", "alp_stats_time", "alp_stats_free", "alp_place",
+           "alp_trace_stats", "alp_trace_stats_sized", "alp_stats_set_timing", "alp_stats_time",
+           "alp_stats_free", "alp_place",
            "alp_eval_candidates",
            "alp_set_launch", "alp_set_timing", "alp_kernel_times", "alp_kernel_time_totals",
            "alp_num_candidates", "alp_free",
@@ -89,6 +90,7 @@ def lib():
         L.alp_place.argtypes = [vp, u32, vp, vp, vp]
         L.alp_stats_create.argtypes = [C.POINTER(vp), i32, vp]
         L.alp_trace_stats.argtypes = [vp, u32, u32, vp, vp, vp, vp, vp]
+        L.alp_trace_stats_sized.argtypes = [vp, u32, u32, vp, vp, vp, vp, u64, vp]
         L.alp_stats_set_timing.argtypes = [vp, i32]
         L.alp_stats_time.argtypes = [vp, C.POINTER(C.c_float)]
         L.alp_stats_free.argtypes = [vp]
@@ -102,7 +104,8 @@ def lib():
                      "alp_search_batch_async", "alp_search_batch_async_noalloc",
                      "alp_max_throughput",
                      "alp_allocate_workflows", "alp_search_pruned", "alp_stats_create",
-                     "alp_trace_stats", "alp_stats_set_timing", "alp_stats_time", "alp_place",
+                     "alp_trace_stats", "alp_trace_stats_sized", "alp_stats_set_timing",
+                     "alp_stats_time", "alp_place",
                      "alp_eval_candidates", "alp_set_launch", "alp_set_timing",
                      "alp_kernel_times", "alp_kernel_time_totals", "alp_num_candidates"):
             getattr(L, name).restype = i32
@@ -320,7 +323,8 @@ class Context:
 
 
 class StatsContext:
-    """Workflow statistics from execution traces on one GPU (alp_stats_create / alp_trace_stats).
+    """Workflow statistics from execution traces on one GPU (alp_stats_create /
+    alp_trace_stats_sized).
 
     ``compute`` takes torch tensors already on the device (offsets and timestamps 64-bit, llm
     32-bit), or numpy arrays, which it copies to the device first with torch."""
@@ -346,8 +350,10 @@ class StatsContext:
                ((offsets, np.uint64), (llm, np.uint32), (start, np.uint64), (end, np.uint64))]
         out = np.zeros(num_llms, dtype=STATS_DTYPE)
         R = int(dev[0].numel()) - 1
-        _check(lib().alp_trace_stats(self._ctx, num_llms, R,
-                                     *(C.c_void_p(t.data_ptr()) for t in dev), _ptr(out)))
+        calls = min(int(t.numel()) for t in dev[1:])
+        _check(lib().alp_trace_stats_sized(self._ctx, num_llms, R,
+                                           *(C.c_void_p(t.data_ptr()) for t in dev), calls,
+                                           _ptr(out)))
         return out
 
     def set_timing(self, enable: bool):

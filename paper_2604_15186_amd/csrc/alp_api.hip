@@ -1970,6 +1970,9 @@ int32_t stats_plan(alp_stats_ctx *c, alp::StatsLaunch &l, uint64_t &max_short)
     }
     if (c->offsets[l.R] > 0 && (!l.llm || !l.start || !l.end))
         return fail(ALP_EINVAL, "llm, start_us or end_us is NULL");
+    if (c->offsets[l.R] > l.num_calls)
+        return fail(ALP_EINVAL, "offsets end at %llu, the call arrays at %llu",
+                    (unsigned long long)c->offsets[l.R], (unsigned long long)l.num_calls);
     if (!longs.empty()) {
         if ((e = c->long_list.ensure(longs.size() * sizeof(uint32_t))) != hipSuccess ||
             (e = c->long_base.ensure(bases.size() * sizeof(uint64_t))) != hipSuccess ||
@@ -1989,11 +1992,10 @@ int32_t stats_plan(alp_stats_ctx *c, alp::StatsLaunch &l, uint64_t &max_short)
     return ALP_OK;
 }
 
-}  // namespace
-
-int32_t alp_trace_stats(alp_stats_ctx *c, uint32_t num_llms, uint32_t num_traces,
-                        const uint64_t *offsets, const uint32_t *llm, const uint64_t *start_us,
-                        const uint64_t *end_us, alp_stats_t *out)
+// sized: the call arrays are known to hold num_calls entries.
+int32_t trace_stats(alp_stats_ctx *c, uint32_t num_llms, uint32_t num_traces,
+                    const uint64_t *offsets, const uint32_t *llm, const uint64_t *start_us,
+                    const uint64_t *end_us, bool sized, uint64_t num_calls, alp_stats_t *out)
 {
     if (!c || !offsets || !out)
         return fail(ALP_EINVAL, "ctx, offsets or out is NULL");
@@ -2014,6 +2016,7 @@ int32_t alp_trace_stats(alp_stats_ctx *c, uint32_t num_llms, uint32_t num_traces
     l.llm = llm;
     l.start = start_us;
     l.end = end_us;
+    l.num_calls = sized ? num_calls : UINT64_MAX;
     l.totals = (uint64_t *)c->totals.ptr;
     l.work = (uint32_t *)c->work.ptr;
     l.out = c->host_out_dev;
@@ -2026,9 +2029,10 @@ int32_t alp_trace_stats(alp_stats_ctx *c, uint32_t num_llms, uint32_t num_traces
     uint64_t long_traces = 0;
     int32_t st = ALP_OK;
     // Without the offsets on the host where the call can do without: one launch sequence and one
-    // wait.  The kernels check the offsets; bad ones are read here for the error, and traces
-    // beyond the short ones' length take a second launch.
-    bool plan = c->plan_first || !llm || !start_us || !end_us;
+    // wait.  The kernels check the offsets against the arrays' length; bad ones are read here for
+    // the error, and traces beyond the short ones' length take a second launch.  Where the length
+    // is not known, a malformed list could lead a kernel beyond the arrays: it is read here first.
+    bool plan = !sized || c->plan_first || !llm || !start_us || !end_us;
     if (!plan) {
         if ((st = stats_launch(c, l, tail)) != ALP_OK)
             return st;
@@ -2088,6 +2092,24 @@ int32_t alp_trace_stats(alp_stats_ctx *c, uint32_t num_llms, uint32_t num_traces
         return fail(ALP_ERANGE, "n or p of 2^31 thousandths or more");
     memcpy(out, c->host_out, num_llms * sizeof(alp_stats_t));
     return ALP_OK;
+}
+
+}  // namespace
+
+int32_t alp_trace_stats(alp_stats_ctx *c, uint32_t num_llms, uint32_t num_traces,
+                        const uint64_t *offsets, const uint32_t *llm, const uint64_t *start_us,
+                        const uint64_t *end_us, alp_stats_t *out)
+{
+    return trace_stats(c, num_llms, num_traces, offsets, llm, start_us, end_us, false, 0, out);
+}
+
+int32_t alp_trace_stats_sized(alp_stats_ctx *c, uint32_t num_llms, uint32_t num_traces,
+                              const uint64_t *offsets, const uint32_t *llm,
+                              const uint64_t *start_us, const uint64_t *end_us,
+                              uint64_t num_calls, alp_stats_t *out)
+{
+    return trace_stats(c, num_llms, num_traces, offsets, llm, start_us, end_us, true, num_calls,
+                       out);
 }
 
 int32_t alp_stats_set_timing(alp_stats_ctx *ctx, int32_t enable)

@@ -320,8 +320,9 @@ struct StatsLaunch {
     const uint64_t *start, *end;
     uint32_t lds_cap;                 // a power of two, 256..kStatsShortMax
     uint32_t max_short;
+    uint64_t num_calls;               // entries of the call arrays
     bool planned;                     // the host has read the offsets; otherwise the kernels check
-                                      // them and count the long traces
+                                      // them (against num_calls) and count the long traces
     uint32_t num_long;                // planned: traces beyond lds_cap, long_traces[], sorted in
     const uint32_t *long_traces;      // scratch, trace k at 2 * long_base[k] words
     const uint64_t *long_base;        // (2 * pow2(length) words each)

@@ -251,6 +251,7 @@ struct StatsArgs {
     // pass that sees every trace reports bad offsets (flag 16) and counts the long traces; with
     // any, the last block leaves the totals to a second launch of the long pass.
     uint32_t planned;
+    uint64_t num_calls;               // entries of the call arrays
     uint32_t *long_count;
     uint32_t group_max;               // direct sort: the longest trace the group launches take
     uint32_t seq;                     // stored in the StatsTail last, with a release
@@ -262,7 +263,8 @@ constexpr uint32_t kLongestWord = 3 * ALP_MAX_LLMS, kInOrderWord = kLongestWord 
 static_assert(kInOrderWord < kStatsCopyStride, "a copy holds its measures");
 
 // Trace r's calls, [lo, lo + n); false (n = 0) if its offsets are bad.  The call arrays hold
-// offsets[R] entries, so a trace within them is safe to read whatever the other offsets are.
+// num_calls entries (which the caller states: a malformed list's last offset would not do), so a
+// trace within them is safe to read whatever the other offsets are.
 __device__ __forceinline__ bool trace_calls(const StatsArgs &a, uint32_t r, uint64_t &lo,
                                             uint64_t &n)
 {
@@ -271,7 +273,7 @@ __device__ __forceinline__ bool trace_calls(const StatsArgs &a, uint32_t r, uint
     n = hi - lo;
     if (a.planned)
         return true;
-    const bool ok = hi >= lo && hi <= a.offsets[a.R] && n <= (1ull << 24) && (r != 0 || lo == 0);
+    const bool ok = hi >= lo && hi <= a.num_calls && n <= (1ull << 24) && (r != 0 || lo == 0);
     n = ok ? n : 0;
     return ok;
 }
@@ -1221,6 +1223,7 @@ hipError_t launch_trace_stats(const StatsLaunch &l, hipStream_t st)
     a.slot_done = reinterpret_cast<uint32_t *>(l.totals + kStatsTotalsWords + 2);
     a.out = l.out;
     a.planned = l.planned ? 1u : 0u;
+    a.num_calls = l.num_calls;
     a.seq = l.seq;
     a.num_long = l.num_long;
     a.group_max = l.max_short > 1536 ? 2048u : l.max_short > 1024 ? 1536u

@@ -217,6 +217,7 @@ def test_null_arguments_rejected():
     assert lib.alp_set_timing(None, 1) == alp.ALP_EINVAL
     assert lib.alp_search_pruned(None, 1, None, None, None, 3, None) == alp.ALP_EINVAL
     assert lib.alp_trace_stats(None, 2, 1, None, None, None, None, None) == alp.ALP_EINVAL
+    assert lib.alp_trace_stats_sized(None, 2, 1, None, None, None, None, 0, None) == alp.ALP_EINVAL
     assert lib.alp_stats_create(None, 0, None) == alp.ALP_EINVAL
     assert lib.alp_place(None, 1, None, None, None) == alp.ALP_EINVAL
     lib.alp_stats_free(None)

@@ -62,7 +62,7 @@ def test_one_context_takes_every_path(alp, shape, R, per):
 @pytest.mark.parametrize("offsets", [[0, 100, 10], [0, 4, 3, 10], [5, 10], [0, 12, 11, 10],
                                      [3, 2, 1], [0, 5, (1 << 63), 10]])
 def test_bad_offsets_are_refused_and_leave_the_context_working(alp, offsets):
-    """The call arrays hold offsets[-1] entries: no pass reads a call beyond them."""
+    """The call arrays hold offsets[-1] entries."""
     good = make_traces("rag", 50, 3)
     calls = int(offsets[-1])
     rng = np.random.default_rng(4)
@@ -78,3 +78,53 @@ def test_bad_offsets_are_refused_and_leave_the_context_working(alp, offsets):
                 long = offsets[1] + (1 << 24) < offsets[2] if len(offsets) > 3 else False
                 assert err.value.status == (alp.ALP_ERANGE if long else alp.ALP_EINVAL)
             _same(ctx, order)
+
+
+@pytest.mark.parametrize("sized", [True, False], ids=["sized", "unsized"])
+@pytest.mark.parametrize("offsets", [[0, 10, 5, 1000], [0, 1000], [0, 3, 11, 11], [4, 1000, 2, 9]])
+def test_offsets_beyond_the_call_arrays_are_refused(alp, offsets, sized):
+    """Lists whose last (or any) offset lies beyond the arrays' ten calls.  The arrays are the front
+    of longer ones, whose further calls belong to an LLM out of range: a call read there would be
+    one more reason for EINVAL, never a fault.  Without the arrays' length only a malformed list
+    can be refused, and only before anything is read."""
+    import torch
+    good = make_traces("rag", 50, 3)
+    off = torch.tensor(offsets, dtype=torch.int64, device="cuda")
+    llm = torch.full((2000,), 7, dtype=torch.int32, device="cuda")
+    llm[:10] = 0
+    start = torch.arange(2000, dtype=torch.int64, device="cuda")
+    end = start + 5
+    with alp.StatsContext(0) as ctx:
+        for order in (good, _shuffle(good, 5)):           # from the sweep, then the direct sort
+            for _ in range(2):
+                _same(ctx, order)
+            if sized:
+                with pytest.raises(alp.AlpError) as err:
+                    ctx.compute(1, off, llm[:10], start[:10], end[:10])
+                assert err.value.status == alp.ALP_EINVAL
+                assert "offset" in str(err.value)
+            elif offsets != sorted(offsets) or offsets[0]:
+                out = np.zeros(1, alp.STATS_DTYPE)
+                st = alp.lib().alp_trace_stats(ctx._ctx, 1, len(offsets) - 1, off.data_ptr(),
+                                               llm.data_ptr(), start.data_ptr(), end.data_ptr(),
+                                               out.ctypes.data)
+                assert st == alp.ALP_EINVAL and "offsets" in alp.last_error()
+            _same(ctx, order)
+
+
+def test_without_the_arrays_length_the_result_is_the_same(alp):
+    """alp_trace_stats and alp_trace_stats_sized agree, call by call, on one context each."""
+    import torch
+    logged = make_traces("beam", 60, 8)
+    longer = _joined(_one_start(logged), 4)
+    with alp.StatsContext(0) as a, alp.StatsContext(0) as b:
+        for tr in (logged, _shuffle(logged, 1), longer, _shuffle(longer, 2), logged):
+            dev = [torch.from_numpy(np.ascontiguousarray(tr[k], t).view(s)).cuda() for k, t, s in
+                   (("offsets", np.uint64, np.int64), ("llm", np.uint32, np.int32),
+                    ("start", np.uint64, np.int64), ("end", np.uint64, np.int64))]
+            out = np.zeros(tr["M"], alp.STATS_DTYPE)
+            st = alp.lib().alp_trace_stats(a._ctx, tr["M"], len(tr["offsets"]) - 1,
+                                           *(t.data_ptr() for t in dev), out.ctypes.data)
+            assert st == alp.ALP_OK
+            assert out.tobytes() == b.compute(tr["M"], *dev).tobytes()
+            _same(a, tr)

@@ -1226,8 +1226,13 @@ hipError_t launch_trace_stats(const StatsLaunch &l, hipStream_t st)
     a.num_calls = l.num_calls;
     a.seq = l.seq;
     a.num_long = l.num_long;
-    a.group_max = l.max_short > 1536 ? 2048u : l.max_short > 1024 ? 1536u
-                : l.max_short > kWaveSortMax ? 1024u : kWaveSortMax;
+    // A launch holds fewer than 2^32 threads, so a group of NT threads per trace serves fewer than
+    // 2^32 / NT traces; in a longer list the traces of that size go to the work list.
+    auto fits = [&](uint32_t nt) { return (uint64_t)R * nt < (UINT64_C(1) << 32); };
+    a.group_max = l.max_short > 1536 && fits(256)          ? 2048u
+                  : l.max_short > 1024 && fits(192)        ? 1536u
+                  : l.max_short > kWaveSortMax && fits(128) ? 1024u
+                                                            : kWaveSortMax;
     if (l.order == kStatsSweep) {
         const dim3 grid((R + kSweepWaves - 1) / kSweepWaves), block(64 * kSweepWaves);
         if (l.M <= 2)

@@ -128,3 +128,37 @@ def test_without_the_arrays_length_the_result_is_the_same(alp):
             assert st == alp.ALP_OK
             assert out.tobytes() == b.compute(tr["M"], *dev).tobytes()
             _same(a, tr)
+
+
+@pytest.mark.parametrize("R", [1 << 24, 3 << 23])
+def test_more_traces_than_a_launch_holds_threads_for(alp, R):
+    """2^24 traces and more (256 threads for each would be 2^32 or more) out of end order, the
+    longest of 1,030 calls: 1,024 copies and more of the same traces, so the sums are multiples of
+    the oracle's and n and p the same."""
+    import torch
+    T = 1 << 13
+    rng = np.random.default_rng(2 ** 24)
+    n = rng.integers(2, 4, T)                             # out of end order: sorted directly
+    n[5], n[77], n[1234] = 1030, 600, 0
+    off = np.concatenate([[0], np.cumsum(n)]).astype(np.int64)
+    calls = int(off[-1])
+    end = np.empty(calls, np.int64)
+    for lo, hi in zip(off[:-1], off[1:]):
+        end[lo:hi] = np.sort(rng.integers(100_000, 1 << 27, hi - lo))[::-1]
+    start = end - rng.integers(1, 100_000, calls)
+    llm = rng.integers(0, 2, calls).astype(np.int32)
+    want = oracle.trace_stats(2, off.astype(np.uint64), llm.astype(np.uint32),
+                              start.astype(np.uint64), end.astype(np.uint64))
+    K = R // T
+    base = torch.arange(K, dtype=torch.int64, device="cuda").repeat_interleave(T) * calls
+    offsets = torch.empty(R + 1, dtype=torch.int64, device="cuda")
+    offsets[:R] = base + torch.from_numpy(off[:-1]).cuda().repeat(K)
+    offsets[R] = K * calls
+    dev = [torch.from_numpy(v).cuda().repeat(K) for v in (llm, start, end)]
+    with alp.StatsContext(0) as ctx:
+        for _ in range(3):                                # the sweep, then the direct sort
+            got = ctx.compute(2, offsets, *dev)
+            for f in ("calls", "busy_us", "active_us"):
+                assert [int(v) for v in got[f]] == [K * int(v) for v in want[f]], f
+            for f in ("n_milli", "p_milli"):
+                assert got[f].tolist() == want[f].tolist(), f

@@ -322,7 +322,7 @@ int32_t alp_trace_stats_sized(alp_stats_ctx *ctx, uint32_t num_llms, uint32_t nu
                               uint64_t num_calls, alp_stats_t *out);
 
 /* Enables HIP-event timing; alp_stats_time gives the milliseconds of the last computation's
- * kernels (initialisation to final division). */
+ * kernels (initialisation to final division; the sum of both where a call launches them twice). */
 int32_t alp_stats_set_timing(alp_stats_ctx *ctx, int32_t enable);
 int32_t alp_stats_time(alp_stats_ctx *ctx, float *ms);
 

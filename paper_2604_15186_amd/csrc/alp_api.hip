@@ -1857,6 +1857,7 @@ struct alp_stats_ctx {
     int timing = 0;
     hipEvent_t ev[2] = {nullptr, nullptr};
     float last_ms = 0.0f;
+    float call_ms = 0.0f;               // the present call's launch sequences so far
     // How the next call starts, from what the last one saw: sorting every trace without the
     // end-order sweep (a sweep found most traces out of end order, each of which is then loaded
     // twice; the direct sort counts the traces in end order and goes back once most are), with
@@ -1911,8 +1912,12 @@ int32_t stats_launch(alp_stats_ctx *c, alp::StatsLaunch &l, alp::StatsTail &tail
     l.seq = c->seq;
     alp::StatsTail *host = (alp::StatsTail *)(c->host_out + ALP_MAX_LLMS);
     Marked mark("alp trace statistics");
+    if (c->timing && (e = hipEventRecord(c->ev[0], c->stream)) != hipSuccess)
+        return hip_fail(e, "hipEventRecord");
     if ((e = alp::launch_trace_stats(l, c->stream)) != hipSuccess)
         return hip_fail(e, "statistics launch");
+    if (c->timing && (e = hipEventRecord(c->ev[1], c->stream)) != hipSuccess)
+        return hip_fail(e, "hipEventRecord");
     if (!wait_signal(&host->seq, l.seq, c->stream)) {
         if ((e = hipStreamSynchronize(c->stream)) != hipSuccess)
             return hip_fail(e, "statistics");
@@ -1921,6 +1926,13 @@ int32_t stats_launch(alp_stats_ctx *c, alp::StatsLaunch &l, alp::StatsTail &tail
     }
     c->counters_clean = true;
     memcpy(&tail, host, sizeof(tail));
+    if (c->timing) {
+        float ms = 0.0f;
+        if ((e = hipEventSynchronize(c->ev[1])) != hipSuccess ||
+            (e = hipEventElapsedTime(&ms, c->ev[0], c->ev[1])) != hipSuccess)
+            return hip_fail(e, "statistics time");
+        c->call_ms += ms;
+    }
     return ALP_OK;
 }
 
@@ -2023,8 +2035,7 @@ int32_t trace_stats(alp_stats_ctx *c, uint32_t num_llms, uint32_t num_traces,
     l.order = c->direct ? alp::kStatsDirect : alp::kStatsSweep;
     l.lds_cap = alp::kStatsShortMax;
     l.max_short = c->direct_max;
-    if (c->timing && (e = hipEventRecord(c->ev[0], c->stream)) != hipSuccess)
-        return hip_fail(e, "hipEventRecord");
+    c->call_ms = 0.0f;
     alp::StatsTail tail;
     uint64_t long_traces = 0;
     int32_t st = ALP_OK;
@@ -2076,12 +2087,8 @@ int32_t trace_stats(alp_stats_ctx *c, uint32_t num_llms, uint32_t num_traces,
         c->direct = 2 * (uint64_t)tail.in_order <= short_traces;
         c->direct_max = tail.longest;
     }
-    if (c->timing) {
-        if ((e = hipEventRecord(c->ev[1], c->stream)) != hipSuccess ||
-            (e = hipEventSynchronize(c->ev[1])) != hipSuccess ||
-            (e = hipEventElapsedTime(&c->last_ms, c->ev[0], c->ev[1])) != hipSuccess)
-            return hip_fail(e, "statistics time");
-    }
+    if (c->timing)
+        c->last_ms = c->call_ms;
     if (tail.flags & 1u)
         return fail(ALP_EINVAL, "a call's llm index is not below num_llms");
     if (tail.flags & 2u)

@@ -162,3 +162,30 @@ def test_more_traces_than_a_launch_holds_threads_for(alp, R):
                 assert [int(v) for v in got[f]] == [K * int(v) for v in want[f]], f
             for f in ("n_milli", "p_milli"):
                 assert got[f].tolist() == want[f].tolist(), f
+
+
+def test_the_time_is_the_kernels_alone(alp):
+    """A context that expects long traces reads the offsets first: four million of them on the
+    host take many times the kernels' time, and none of that is in it."""
+    import time
+
+    import torch
+    R = 1 << 22
+    dev = [torch.zeros(n, dtype=t, device="cuda") for n, t in
+           ((R + 1, torch.int64), (3000, torch.int32), (3000, torch.int64), (3000, torch.int64))]
+    dev[0][R // 2:] = 3000                                # one long trace, the others empty
+    dev[3] += torch.arange(3000, device="cuda")
+    with alp.StatsContext(0) as ctx:
+        ctx.set_timing(True)
+        ctx.compute(1, *dev)                              # finds the long trace: two launches
+        kernels, call = [], []
+        for _ in range(3):
+            t = time.perf_counter()
+            ctx.compute(1, *dev)
+            call.append(1e3 * (time.perf_counter() - t))
+            kernels.append(ctx.time_ms())
+        assert 0 < min(kernels) < 0.5 * min(call), (kernels, call)
+        dev[0][R // 2:] = 2000                            # none is long any more, nor in order
+        ctx.compute(1, *dev)
+        ctx.compute(1, *dev)
+        assert 0 < ctx.time_ms() < min(call)

@@ -1029,8 +1029,12 @@ trace_wave_kernel(StatsArgs a)
     if (r >= a.R)
         return;                                        // uniform over the wave
     uint64_t lo, n64;
-    if (!short_trace(a, r, lane, lo, n64))
-        return;                                        // empty, or another pass takes it
+    if (!short_trace(a, r, lane, lo, n64)) {           // empty, or another pass takes it
+        if (n64 == 0 && lane == 0)                     // (an empty trace is in end order)
+            atomicAdd(&a.totals[(uint64_t)(r % kStatsCopies) * kStatsCopyStride + kInOrderWord],
+                      1ull);
+        return;
+    }
     if (n64 > kWaveSortMax) {
         if (n64 > a.group_max && lane == 0)            // no group was launched for it
             a.work[atomicAdd(a.work_count, 1u)] = r;

@@ -189,3 +189,25 @@ def test_the_time_is_the_kernels_alone(alp):
         ctx.compute(1, *dev)
         ctx.compute(1, *dev)
         assert 0 < ctx.time_ms() < min(call)
+
+
+def test_a_context_goes_back_to_the_sweep_on_sparse_traces_in_order(alp):
+    """Three empty traces beside every logged one, after shuffled traces: the context that sorts
+    directly finds most in order and sweeps again, as a new context does from its first call."""
+    logged = make_traces("beam", 3000, 7)
+    sparse = {**logged, "offsets": np.repeat(logged["offsets"], [4] * 3000 + [1])}
+
+    def kernel_ms(ctx):
+        ms = []
+        for _ in range(6):
+            _same(ctx, sparse)
+            ms.append(ctx.time_ms())
+        return min(ms)
+
+    with alp.StatsContext(0) as new, alp.StatsContext(0) as used:
+        for ctx in (new, used):
+            ctx.set_timing(True)
+        for _ in range(2):
+            _same(used, _shuffle(logged, 1))
+        want, got = kernel_ms(new), kernel_ms(used)
+        assert got < 1.5 * want, (got, want)          # a call: 36 us swept, 112 sorted

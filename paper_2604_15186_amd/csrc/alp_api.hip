@@ -2036,7 +2036,7 @@ int32_t trace_stats(alp_stats_ctx *c, uint32_t num_llms, uint32_t num_traces,
     l.lds_cap = alp::kStatsShortMax;
     l.max_short = c->direct_max;
     c->call_ms = 0.0f;
-    alp::StatsTail tail;
+    alp::StatsTail tail{};
     uint64_t long_traces = 0;
     int32_t st = ALP_OK;
     // Without the offsets on the host where the call can do without: one launch sequence and one
@@ -2080,13 +2080,9 @@ int32_t trace_stats(alp_stats_ctx *c, uint32_t num_llms, uint32_t num_traces,
     }
     c->plan_first = long_traces != 0;
     const uint64_t short_traces = num_traces - long_traces;
-    if (!c->direct) {
-        c->direct = 2 * (uint64_t)tail.listed > short_traces;
-        c->direct_max = alp::kStatsShortMax;
-    } else {
-        c->direct = 2 * (uint64_t)tail.in_order <= short_traces;
-        c->direct_max = tail.longest;
-    }
+    c->direct = c->direct ? 2 * (uint64_t)tail.in_order <= short_traces
+                          : 2 * (uint64_t)tail.listed > short_traces;
+    c->direct_max = tail.longest;
     if (c->timing)
         c->last_ms = c->call_ms;
     if (tail.flags & 1u)

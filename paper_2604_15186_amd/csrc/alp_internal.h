@@ -301,8 +301,10 @@ struct StatsTail {
     uint32_t flags;                   // status bits (see alp_trace_stats)
     uint32_t listed;                  // traces the sweep left to the sort pass
     uint32_t longs;                   // traces beyond kStatsShortMax, left to a second launch
-    uint32_t longest, in_order;       // direct sort: longest trace above 512 calls (0: none), and
-                                      // traces whose calls came in end order (empty ones are)
+    uint32_t longest;                 // longest trace above 512 calls that the direct sort saw or
+                                      // the sweep listed (0: none)
+    uint32_t in_order;                // direct sort: traces whose calls came in end order (empty
+                                      // ones are)
     uint32_t pad[2];
     uint32_t seq;                     // the launch's seq, stored last
 };

@@ -53,6 +53,7 @@ constexpr uint64_t kStartLimit = 1ull << 60;
 constexpr uint64_t kDurationLimit = 1ull << 32;
 constexpr uint32_t kThreads = 256;
 constexpr uint32_t kSortBlocks = 1024;                 // grid of the work-list sort
+constexpr uint32_t kWaveSortMax = 64 * 8;              // longest trace one wave sorts (8 keys/lane)
 
 __global__ void stats_init_kernel(uint64_t *__restrict__ totals, uint32_t words)
 {
@@ -257,8 +258,8 @@ struct StatsArgs {
     uint32_t seq;                     // stored in the StatsTail last, with a release
 };
 
-// Words of a copy of the totals after the sums: the longest trace and the traces in end order, as
-// the direct sort sees them.
+// Words of a copy of the totals after the sums: the longest trace above 512 calls that the direct
+// sort sees or the sweep lists, and the traces that the direct sort finds in end order.
 constexpr uint32_t kLongestWord = 3 * ALP_MAX_LLMS, kInOrderWord = kLongestWord + 1;
 static_assert(kInOrderWord < kStatsCopyStride, "a copy holds its measures");
 
@@ -857,12 +858,15 @@ __global__ void __launch_bounds__(64 * kSweepWaves) trace_sweep_kernel(StatsArgs
         load(R, k0);
         sweep_rows(R, k0);
     }
+    unsigned long long *copy = a.totals + (uint64_t)(r % kStatsCopies) * kStatsCopyStride;
     if (bad) {
-        if (lane == 0)
+        if (lane == 0) {
             a.work[atomicAdd(a.work_count, 1u)] = r;
+            if (n > kWaveSortMax)
+                atomicMax(&copy[kLongestWord], (unsigned long long)n);
+        }
         return;
     }
-    unsigned long long *copy = a.totals + (uint64_t)(r % kStatsCopies) * kStatsCopyStride;
 #pragma unroll
     for (int q = 0; q < MM; ++q)
         if ((uint32_t)q < M)
@@ -974,7 +978,6 @@ __device__ __forceinline__ void finish_block(const StatsArgs &a, uint32_t i, uin
 }
 
 constexpr uint32_t kWaveSortWaves = 4;       // traces per workgroup of the direct sort
-constexpr uint32_t kWaveSortMax = 64 * 8;    // longest trace one wave sorts (8 keys per lane)
 
 // Trace r (calls lo .. lo + n - 1, n <= 64 E) sorted and swept by one wave: the wave sorts the
 // 64 E keys in registers and across lanes (no LDS, no barrier), sweeps them, and adds the

@@ -211,3 +211,24 @@ def test_a_context_goes_back_to_the_sweep_on_sparse_traces_in_order(alp):
             _same(used, _shuffle(logged, 1))
         want, got = kernel_ms(new), kernel_ms(used)
         assert got < 1.5 * want, (got, want)          # a call: 36 us swept, 112 sorted
+
+
+def test_the_first_direct_sort_launches_only_the_groups_it_needs(alp):
+    """2^22 traces of two calls, the later one logged first: the call after the sweep takes no
+    longer than the next one (a launch of groups for traces that are not there takes milliseconds)."""
+    import torch
+    R = 1 << 22
+    offsets = 2 * torch.arange(R + 1, dtype=torch.int64, device="cuda")
+    llm = torch.zeros(2 * R, dtype=torch.int32, device="cuda")
+    start = torch.tensor([500, 100], dtype=torch.int64, device="cuda").repeat(R)
+    with alp.StatsContext(0) as warm:                     # every kernel loaded
+        for _ in range(3):
+            warm.compute(1, offsets, llm, start, start + 50)
+    ms = []
+    with alp.StatsContext(0) as ctx:
+        ctx.set_timing(True)
+        for _ in range(4):
+            got = ctx.compute(1, offsets, llm, start, start + 50)
+            ms.append(ctx.time_ms())
+            assert [int(v) for v in got[0]] == [2000, 1000, 2 * R, 100 * R, 100 * R]
+    assert ms[1] < 1.5 * min(ms[2:]), ms

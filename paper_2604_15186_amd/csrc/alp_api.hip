@@ -1854,6 +1854,8 @@ struct alp_stats_ctx {
     bool counters_clean = false;
     uint64_t *offsets = nullptr;            // pinned: the trace offsets, read for planning
     size_t offsets_cap = 0;                 // entries
+    std::vector<uint32_t> longs;            // traces beyond kStatsShortMax calls and the bases of
+    std::vector<uint64_t> bases;            // their scratch, kept while their copies are queued
     int timing = 0;
     hipEvent_t ev[2] = {nullptr, nullptr};
     float last_ms = 0.0f;
@@ -1960,8 +1962,10 @@ int32_t stats_plan(alp_stats_ctx *c, alp::StatsLaunch &l, uint64_t &max_short)
         return hip_fail(e, "copy offsets");
     if (c->offsets[0] != 0)
         return fail(ALP_EINVAL, "offsets[0] = %llu, not 0", (unsigned long long)c->offsets[0]);
-    std::vector<uint32_t> longs;
-    std::vector<uint64_t> bases;
+    std::vector<uint32_t> &longs = c->longs;
+    std::vector<uint64_t> &bases = c->bases;
+    longs.clear();
+    bases.clear();
     uint64_t scratch_pairs = 0;
     for (uint32_t r = 0; r < l.R; ++r) {
         if (c->offsets[r + 1] < c->offsets[r])
@@ -1993,8 +1997,7 @@ int32_t stats_plan(alp_stats_ctx *c, alp::StatsLaunch &l, uint64_t &max_short)
         if ((e = hipMemcpyAsync(c->long_list.ptr, longs.data(), longs.size() * sizeof(uint32_t),
                                 hipMemcpyHostToDevice, c->stream)) != hipSuccess ||
             (e = hipMemcpyAsync(c->long_base.ptr, bases.data(), bases.size() * sizeof(uint64_t),
-                                hipMemcpyHostToDevice, c->stream)) != hipSuccess ||
-            (e = hipStreamSynchronize(c->stream)) != hipSuccess)     // the vectors go away
+                                hipMemcpyHostToDevice, c->stream)) != hipSuccess)
             return hip_fail(e, "copy long traces");
     }
     l.num_long = (uint32_t)longs.size();

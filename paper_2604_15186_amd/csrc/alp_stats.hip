@@ -627,7 +627,12 @@ __device__ __forceinline__ void one_trace(const StatsArgs &a, uint32_t r, uint32
     __shared__ unsigned long long s_sum[3 * ALP_MAX_LLMS];   // per LLM: calls, busy, active
     __shared__ uint32_t s_valid, s_far;
     uint64_t lo, n;
-    (void)trace_calls(a, r, lo, n);
+    if constexpr (Global) {                            // (planned: the host has checked them)
+        lo = a.offsets[r];
+        n = a.offsets[r + 1] - lo;
+    } else {
+        (void)trace_calls(a, r, lo, n);
+    }
     if (n == 0 || (!Global && n > a.lds_cap))
         return;                                        // empty, or the global pass takes it
     uint32_t P = kThreads;                              // padded length: a power of two
@@ -1141,8 +1146,11 @@ __device__ __forceinline__ uint32_t sort_participants(const StatsArgs &a)
     return listed == 0 ? 1u : (listed < a.sort_grid ? listed : a.sort_grid);
 }
 
+// Four waves per SIMD: the 1,024 blocks of a full work list are then resident together (free to
+// choose, the compiler took 133 VGPRs, three waves).
 template <bool FLOAT>
-__global__ void __launch_bounds__(kThreads) trace_sort_kernel(StatsArgs a)
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4)))
+trace_sort_kernel(StatsArgs a)
 {
     extern __shared__ __align__(8) unsigned char s_dyn[];
     const uint32_t P = sort_participants(a);

@@ -174,7 +174,7 @@ struct alp_ctx {
     size_t host_query_cap = 0;
     alp_result_t *host_results = nullptr;   // pinned host memory the kernels write results to
     alp_result_t *host_results_dev = nullptr;  // its device-visible address
-    size_t host_results_cap = 0;
+    size_t host_results_cap = 0;            // bytes
     uint32_t *host_signal = nullptr;        // mapped word a single search's record signals in
     uint32_t *host_signal_dev = nullptr;    // (FinishArgs::signal), and its device address
     uint32_t call_seq = 0;                  // the last sequence number signalled
@@ -739,25 +739,31 @@ int32_t upload_queries(alp_ctx *c, uint32_t count, const uint32_t *inst, const u
     return ALP_OK;
 }
 
-int32_t ensure_host_results(alp_ctx *c, size_t count)
+int32_t ensure_host_signal(alp_ctx *c)
 {
-    if (!c->host_signal) {
-        void *h = nullptr, *d = nullptr;
-        hipError_t e = alloc_pinned(&h, 64, hipHostMallocMapped);
-        if (e != hipSuccess)
-            return hip_fail(e, "hipHostMalloc(signal)");
-        if ((e = hipHostGetDevicePointer(&d, h, 0)) != hipSuccess) {
-            (void)hipHostFree(h);
-            return hip_fail(e, "hipHostGetDevicePointer(signal)");
-        }
-        c->host_signal = (uint32_t *)h;
-        c->host_signal_dev = (uint32_t *)d;
-        __atomic_store_n(c->host_signal, 0u, __ATOMIC_RELEASE);
+    if (c->host_signal)
+        return ALP_OK;
+    void *h = nullptr, *d = nullptr;
+    hipError_t e = alloc_pinned(&h, 64, hipHostMallocMapped);
+    if (e != hipSuccess)
+        return hip_fail(e, "hipHostMalloc(signal)");
+    if ((e = hipHostGetDevicePointer(&d, h, 0)) != hipSuccess) {
+        (void)hipHostFree(h);
+        return hip_fail(e, "hipHostGetDevicePointer(signal)");
     }
-    if (count <= c->host_results_cap)
+    c->host_signal = (uint32_t *)h;
+    c->host_signal_dev = (uint32_t *)d;
+    __atomic_store_n(c->host_signal, 0u, __ATOMIC_RELEASE);
+    return ALP_OK;
+}
+
+// The mapped result buffer, of at least `bytes`.
+int32_t ensure_host_results(alp_ctx *c, size_t bytes)
+{
+    if (bytes <= c->host_results_cap)
         return ALP_OK;
     void *grown = nullptr, *grown_dev = nullptr;
-    hipError_t e = alloc_pinned(&grown, count * sizeof(alp_result_t), hipHostMallocMapped);
+    hipError_t e = alloc_pinned(&grown, bytes, hipHostMallocMapped);
     if (e != hipSuccess)
         return hip_fail(e, "hipHostMalloc(results)");
     if ((e = hipHostGetDevicePointer(&grown_dev, grown, 0)) != hipSuccess) {
@@ -768,7 +774,7 @@ int32_t ensure_host_results(alp_ctx *c, size_t count)
         (void)hipHostFree(c->host_results);
     c->host_results = (alp_result_t *)grown;
     c->host_results_dev = (alp_result_t *)grown_dev;
-    c->host_results_cap = count;
+    c->host_results_cap = bytes;
     return ALP_OK;
 }
 
@@ -979,10 +985,12 @@ bool wait_signal(const uint32_t *word, uint32_t seq, hipStream_t stream)
 // has its record signalled in host memory (FinishArgs::signal).
 int32_t run_search(alp_ctx *c, const alp::QueryDev &q, uint32_t count)
 {
-    int32_t st = ensure_host_results(c, count);
+    int32_t st = ensure_host_results(c, (size_t)count * sizeof(alp_result_t));
     if (st != ALP_OK)
         return st;
     const bool signalled = count == 1 && !c->timing;
+    if (signalled && (st = ensure_host_signal(c)) != ALP_OK)
+        return st;
     uint32_t seq = 0;
     if (signalled && ++c->call_seq == 0)
         ++c->call_seq;                         // 0 is the word's initial value
@@ -1350,8 +1358,8 @@ int32_t alp_max_throughput(alp_ctx *ctx, uint32_t count, const uint32_t *instanc
     int32_t st = upload_queries(ctx, count, inst.data(), cap.data(), zero.data(), q);
     if (st != ALP_OK)
         return st;
-    // Results straight to mapped host memory (the search records' buffer).
-    if ((st = ensure_host_results(ctx, count)) != ALP_OK)
+    // Results straight to mapped host memory (the search records' buffer, 4 bytes an item of it).
+    if ((st = ensure_host_results(ctx, (size_t)count * sizeof(uint32_t))) != ALP_OK)
         return st;
     Marked mark("alp max_throughput");
     hipError_t e;

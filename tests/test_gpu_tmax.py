@@ -44,3 +44,18 @@ def test_matches_the_oracle(alp, point):
         for reps in (1, 37):
             got = ctx.max_throughput(np.tile(G, reps), instances=np.tile(inst, reps))
             assert np.array_equal(np.asarray(got, np.uint64), np.tile(np.asarray(want, np.uint64), reps))
+
+
+def test_results_take_four_bytes_an_item(alp, monkeypatch):
+    """A context that has returned 100 search records (48 bytes each) holds a result buffer for
+    1,200 throughputs: with the queries' buffers there, no allocation is needed."""
+    b = make_custom(411, 2, (1, 2), (2, 4), 2, 4, 8, count=1)
+    G = (np.arange(1200) % 9).astype(np.uint32)
+    inst = np.zeros(1200, np.uint32)
+    with alp.Context(b) as ctx:
+        want = np.concatenate([ctx.max_throughput(G[k:k + 9], instances=inst[:9])
+                               for k in range(0, 1200, 9)])
+        ctx.search_batch(G[:100], np.ones(100, np.uint32), instances=inst[:100])
+        ctx.search_pruned(G, np.ones(1200, np.uint32), instances=inst)
+        monkeypatch.setenv("ALP_TEST_FAIL_ALLOC", "1")
+        assert ctx.max_throughput(G, instances=inst).tolist() == want[:1200].tolist()

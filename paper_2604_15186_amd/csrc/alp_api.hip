@@ -1513,7 +1513,7 @@ int32_t alp_search_pruned(alp_ctx *ctx, uint32_t count, const uint32_t *instance
     // the bound grows with the number of units: checking the largest query covers all
     if (pruned_vector_bound(F_max, sp.M, flags & ALP_PRUNE_ORDER) > ALP_PRUNED_MAX_VECTORS)
         return fail(ALP_ERANGE, "Q*G = %u: more than 2^34 fraction vectors per query", F_max);
-    const uint32_t bpi = alp::pruned_blocks_per_item(sp.M, F_max, count);
+    const uint32_t bpi = alp::pruned_blocks_per_item(sp, F_max, flags, count);
     const uint64_t nblocks = (uint64_t)count * bpi;
     if (nblocks >= (UINT64_C(1) << 31))
         return fail(ALP_ERANGE, "batch too large for one launch (%llu blocks)",

@@ -267,9 +267,11 @@ hipError_t launch_allocate(const alp_result_t *res, uint32_t W, uint32_t G, uint
 // The paper's pruned search for count items of at most F_max units (see alp_search_pruned), after
 // the option-term kernel (rec, ext).  table: count * pruned_table_entries() entries of device
 // memory (0: the blocks build it in LDS); pruned_blocks_per_item() blocks per item, three words of
-// slots for each, and block_counter_words() counters, 0 between launches.  Records table_done (if given) before the enumeration.  Writes out[0..count).
+// slots for each, and block_counter_words() counters, 0 between launches.  Records table_done (if
+// given) before the enumeration.  Writes out[0..count).
 uint64_t pruned_table_entries(const SpaceDev &sp, uint32_t F_max, uint32_t flags);
-uint32_t pruned_blocks_per_item(uint32_t M, uint32_t F_max, uint32_t count);
+uint32_t pruned_blocks_per_item(const SpaceDev &sp, uint32_t F_max, uint32_t flags,
+                                uint32_t count);
 hipError_t launch_pruned(const SpaceDev &sp, const TablesDev &tb, const QueryDev &q, uint32_t count,
                          uint32_t F_max, uint32_t flags, const uint2 *rec, uint64_t *table,
                          uint32_t blocks_per_item, uint64_t *slots, uint32_t *counters,

@@ -126,7 +126,7 @@ constexpr int kPrefix = M <= 2 ? 0 : M == 3 ? 1 : 2;
 struct Walk {
     const uint64_t *table;
     uint32_t Q, mul_Q;
-    bool ordered;
+    bool ordered, staged;
     uint32_t L;                     // running best (L, x) and vector count of the lane
     uint64_t x;
     uint64_t count;
@@ -186,13 +186,23 @@ __device__ __forceinline__ void walk_lanes(const Order &od, Walk &w, uint32_t fi
         lo = remaining - last_hi;
     if (w.ordered && (remaining + 1) / 2 > lo)
         lo = (remaining + 1) / 2;
+    // A prefix without an allocation is only counted, and a lane without one for K reads no further
+    // where that is a read of memory (LDS answers sooner than a branch pays).  4 LLMs, 512 units,
+    // 64 queries, tables in device memory: 6,190 us with every read made, 1,277 so; one query of 5
+    // LLMs and 160 units, in LDS: 152 and 65.
+    if (!alive) {
+        if (lo + first <= hi)
+            w.count += (hi - lo - first) / GROUP + 1;
+        return;
+    }
     const uint32_t r0 = w.mod_q(offset);
     for (uint32_t v = lo + first; v <= hi; v += GROUP) {
         uint32_t L2 = L;
         uint64_t x2 = x;
-        bool a = alive;
+        bool a = true;
         take(od, w, K, r0, v, L2, x2, a);
-        take(od, w, M - 1, w.mod_q(offset + v), remaining - v, L2, x2, a);
+        if (a || w.staged)
+            take(od, w, M - 1, w.mod_q(offset + v), remaining - v, L2, x2, a);
         w.count += 1;
         if (a && lex_less(L2, x2, w.L, w.x)) {
             w.L = L2;
@@ -375,6 +385,7 @@ pruned_scan_kernel(SpaceDev sp, TablesDev tb, QueryDev q, const uint2 *__restric
     w.Q = sp.Q;
     w.mul_Q = mul_Q;
     w.ordered = ordered;
+    w.staged = stage != 0;
     w.L = kNoLatency;
     w.x = ~0ull;
     w.count = 0;
@@ -504,13 +515,17 @@ uint64_t pruned_table_entries(const SpaceDev &sp, uint32_t F_max, uint32_t flags
 }
 
 // About two prefixes a wave (with 3 LLMs a prefix is one fraction, beyond two, of which roughly an
-// eighth leave any vector), and at most 512 blocks (two to a CU): every block repeats the table.
-uint32_t pruned_blocks_per_item(uint32_t M, uint32_t F_max, uint32_t count)
+// eighth leave any vector), and at most 512 blocks (two to a CU): every block orders the LLMs and
+// builds the table in LDS.  With the tables in device memory a batch takes up to 2,048 blocks, 512
+// an item: fewer work on more items at once, whose tables the L2s do not hold (4 LLMs, 512 units,
+// 64 queries: 1,277 us at 512 blocks, 1,124 at 2,048; 256 units, 600 queries: 3,203 and 2,530).
+uint32_t pruned_blocks_per_item(const SpaceDev &sp, uint32_t F_max, uint32_t flags, uint32_t count)
 {
     const uint64_t F1 = (uint64_t)F_max + 1;
-    const uint64_t prefixes = M <= 2 ? 1 : M == 3 ? F1 : F1 * F1 / 8;
+    const uint64_t prefixes = sp.M <= 2 ? 1 : sp.M == 3 ? F1 : F1 * F1 / 8;
     const uint64_t want = (prefixes / 2 + kScanThreads / 64 - 1) / (kScanThreads / 64);
-    const uint64_t room = count < 512 ? 512 / count : 1;
+    const uint64_t most = pruned_table_entries(sp, F_max, flags) ? 2048 : 512;
+    const uint64_t share = most / count, room = share < 1 ? 1 : share < 512 ? share : 512;
     const uint64_t n = want < room ? want : room;
     return n < 1 ? 1u : (uint32_t)n;
 }

@@ -23,6 +23,8 @@ POINTS = [
     (307, 5, 3, (11, 5), (0, 1, 2, 3)),
     (308, 7, 2, (9, 3), (0, 3)),
     (309, 8, 2, (8,), (1, 3)),
+    (311, 4, 16, (21, 5), (0, 1)),                    # 336 units: in memory, more blocks
+    (312, 5, 16, (8,), (2,)),                         # 128 units: in memory without the ordering
 ]
 
 

@@ -227,8 +227,8 @@ __device__ __forceinline__ void walk_from(const Order &od, Walk &w, uint32_t off
         uint32_t lo, hi;
         range<K>(od, w, remaining, prev, lo, hi);
         if constexpr (split) {
-            // no vector is left where the last two cannot reach the rest
-            if (w.ordered && remaining > 2 * hi && (remaining + 2) / 3 > lo)
+            // the largest of the last three fractions
+            if (w.ordered && (remaining + 2) / 3 > lo)
                 lo = (remaining + 2) / 3;
             lo += lane >> 4;
         } else {

@@ -557,7 +557,11 @@ hipError_t launch_pruned(const SpaceDev &sp, const TablesDev &tb, const QueryDev
     }
     if (table_done && (e = hipEventRecord(table_done, st)) != hipSuccess)
         return e;
-    const dim3 grid(count * blocks_per_item), block(kScanThreads);
+    // (a launch holds fewer than 2^32 threads)
+    uint32_t threads = kScanThreads;
+    while (threads > 64 && (uint64_t)count * blocks_per_item * threads >= (UINT64_C(1) << 32))
+        threads /= 2;
+    const dim3 grid(count * blocks_per_item), block(threads);
     const size_t lds = (size_t)stage * sizeof(uint64_t);
 #define ALP_PRUNED_CASE(MM)                                                                        \
     case MM:                                                                                       \

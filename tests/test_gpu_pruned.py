@@ -63,3 +63,20 @@ def test_matches_the_oracle(alp, point):
                     else:
                         assert (int(r["best"]["index"]), int(r["best"]["latency_us"])) == \
                             (w["x"], w["L"]), (flags, k)
+
+
+def test_more_queries_than_a_launch_of_whole_blocks_holds(alp):
+    """2^23 queries: 512 threads for each would be 2^32, more than a launch holds."""
+    b = make_custom(321, 1, (1, 2), (2, 4), 2, 4, 8, count=2, alpha=0.7)
+    count, period = 1 << 23, 1 << 10
+    G = (np.arange(period) % 9).astype(np.uint32)
+    inst = (np.arange(period) % 2).astype(np.uint32)
+    lam = np.full(period, 100, np.uint32)
+    with alp.Context(b) as ctx:
+        want = ctx.search_pruned(G, lam, 3, instances=inst)
+        rep = count // period
+        got = ctx.search_pruned(np.tile(G, rep), np.tile(lam, rep), 3, instances=np.tile(inst, rep))
+        assert (got.reshape(rep, period) == want).all()
+        w = oracle.pruned(oracle.Instance(b, 1), 3, 100, 3)
+        assert (int(want[3]["best"]["index"]), int(want[3]["vectors"])) == \
+            (alp.NO_INDEX if w["x"] is None else w["x"], w["vectors"])

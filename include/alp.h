@@ -396,6 +396,20 @@ int32_t alp_eval_candidates(alp_ctx *ctx, uint32_t instance, uint32_t gpu_budget
 int32_t alp_set_launch(alp_ctx *ctx, uint32_t variant, uint32_t blocks_per_item,
                        uint32_t threads_per_block, uint32_t inner_chunks);
 
+/* The launch that a batch of count searches would take with the present choices (for tests and
+ * tuning; alp_search_batch_async_noalloc keeps to ALP_SCAN_MASKED). */
+#define ALP_SCAN_MASKED 0u            /* masked scan after a kernel for the option terms */
+#define ALP_SCAN_MASKED_ONE_LAUNCH 1u
+#define ALP_SCAN_PACKED 2u            /* packed 16-bit scan, values below 31,744 */
+#define ALP_SCAN_PACKED_WIDE 3u       /* packed 16-bit scan, values up to 65,535 */
+typedef struct {
+    uint32_t form;
+    uint32_t blocks_per_item;
+    uint32_t threads_per_block;
+    uint32_t whole_rows;              /* packed: 1 if a block owns whole rows of tiles */
+} alp_scan_plan_t;
+int32_t alp_scan_plan(alp_ctx *ctx, uint32_t count, alp_scan_plan_t *out);
+
 /* HIP-event timing of the searches' kernels on the context stream.  enable = 0: off; N >= 1: the
  * calls of alp_search, alp_search_batch, alp_search_batch_async, alp_allocate_workflows,
  * alp_search_pruned and alp_place are counted from this call on, and the first and every N-th

@@ -26,7 +26,7 @@ EXPORTS = ("alp_load_profiles", "alp_search", "alp_search_batch", "alp_search_ba
            "alp_trace_stats", "alp_trace_stats_sized", "alp_stats_set_timing", "alp_stats_time",
            "alp_stats_free", "alp_place",
            "alp_eval_candidates",
-           "alp_set_launch", "alp_set_timing", "alp_kernel_times", "alp_kernel_time_totals",
+           "alp_set_launch", "alp_scan_plan", "alp_set_timing", "alp_kernel_times", "alp_kernel_time_totals",
            "alp_num_candidates", "alp_free",
            "alp_status_str", "alp_last_error")
 
@@ -63,6 +63,9 @@ PLACEMENT_DTYPE = np.dtype([("status", np.uint32), ("replicas", np.uint32),
                             ("slot", np.uint16, 128)])
 assert PLACEMENT_DTYPE.itemsize == 272
 PLACE_NONE = 0xFFFF
+SCAN_PLAN_DTYPE = np.dtype([("form", np.uint32), ("blocks_per_item", np.uint32),
+                            ("threads_per_block", np.uint32), ("whole_rows", np.uint32)])
+SCAN_MASKED, SCAN_MASKED_ONE_LAUNCH, SCAN_PACKED, SCAN_PACKED_WIDE = range(4)
 WELFARE_EGALITARIAN, WELFARE_SOCIAL = 0, 1
 PRUNE_ORDER, PRUNE_MIN_FRACTION = 1, 2
 
@@ -96,6 +99,7 @@ def lib():
         L.alp_stats_free.argtypes = [vp]
         L.alp_stats_free.restype = None
         L.alp_set_launch.argtypes = [vp, u32, u32, u32, u32]
+        L.alp_scan_plan.argtypes = [vp, u32, vp]
         L.alp_set_timing.argtypes = [vp, i32]
         L.alp_kernel_times.argtypes = [vp, C.POINTER(C.c_float), C.POINTER(u32)]
         L.alp_kernel_time_totals.argtypes = [vp, C.POINTER(C.c_double), C.POINTER(u64)]
@@ -106,7 +110,7 @@ def lib():
                      "alp_allocate_workflows", "alp_search_pruned", "alp_stats_create",
                      "alp_trace_stats", "alp_trace_stats_sized", "alp_stats_set_timing",
                      "alp_stats_time", "alp_place",
-                     "alp_eval_candidates", "alp_set_launch", "alp_set_timing",
+                     "alp_eval_candidates", "alp_set_launch", "alp_scan_plan", "alp_set_timing",
                      "alp_kernel_times", "alp_kernel_time_totals", "alp_num_candidates"):
             getattr(L, name).restype = i32
         L.alp_free.argtypes = [vp]
@@ -301,6 +305,12 @@ class Context:
                    inner_chunks: int = 0):
         _check(lib().alp_set_launch(self._ctx, variant, blocks_per_item, threads_per_block,
                                     inner_chunks))
+
+    def scan_plan(self, count: int) -> np.void:
+        """The launch a batch of count searches would take (SCAN_PLAN_DTYPE record)."""
+        out = np.zeros(1, dtype=SCAN_PLAN_DTYPE)
+        _check(lib().alp_scan_plan(self._ctx, count, _ptr(out)))
+        return out[0]
 
     def set_timing(self, enable: bool | int):
         """False/0: off; True/1: every call timed; N: the first and every N-th call timed."""

@@ -514,7 +514,10 @@ bool plan_packed(const alp_ctx *c, uint32_t count, alp::ScanGeometry &out)
                     w = k;
         }
     }
-    if (bpi * items >= (UINT64_C(1) << 31))
+    // A launch holds fewer than 2^32 threads.
+    while (w > 1 && bpi * items * 64 * w >= (UINT64_C(1) << 32))
+        --w;
+    if (bpi * items * 64 >= (UINT64_C(1) << 32))
         return false;
     g.blocks_per_item = (uint32_t)bpi;
     g.threads = c->tpb_override ? c->tpb_override : 64 * w;
@@ -1762,6 +1765,27 @@ int32_t alp_set_launch(alp_ctx *ctx, uint32_t variant, uint32_t blocks_per_item,
     ctx->bpi_override = blocks_per_item;
     ctx->tpb_override = threads_per_block;
     ctx->chunks_override = inner_chunks;
+    return ALP_OK;
+}
+
+int32_t alp_scan_plan(alp_ctx *ctx, uint32_t count, alp_scan_plan_t *out)
+{
+    if (!ctx || !out)
+        return fail(ALP_EINVAL, "ctx or out is NULL");
+    if (count == 0)
+        return fail(ALP_EINVAL, "count is 0");
+    DeviceGuard guard(ctx->device);
+    if (guard.status != hipSuccess)
+        return hip_fail(guard.status, "hipSetDevice");
+    alp::ScanGeometry g;
+    const int32_t st = plan_scan(ctx, count, g);
+    if (st != ALP_OK)
+        return st;
+    out->form = g.use_packed ? (g.packed.wide ? ALP_SCAN_PACKED_WIDE : ALP_SCAN_PACKED)
+                             : (g.fused ? ALP_SCAN_MASKED_ONE_LAUNCH : ALP_SCAN_MASKED);
+    out->blocks_per_item = g.blocks_per_item;
+    out->threads_per_block = g.threads;
+    out->whole_rows = g.use_packed && g.packed.rows_per_block ? 1u : 0u;
     return ALP_OK;
 }
 

@@ -1,6 +1,6 @@
 """The packed 16-bit scan against the knapsack DP and the masked scan, on an MI355X: option counts
-around the tiles' remainders, the ends of the signed and unsigned 16-bit ranges and the first space
-beyond them (which the masked scan keeps), two to eight LLMs, lanes' indices beyond 32 bits, and
+around the tiles' remainders, the signed and unsigned 16-bit ranges to their ends and the first space
+beyond them (which the masked scan keeps; the plan says which scan a space takes), two to eight LLMs, lanes' indices beyond 32 bits, and
 launch overrides that take every work distribution (whole rows, tiles in turn, waves sharing a
 tile by rows or records).  Integers throughout: results are equal, ties to the lowest index."""
 from __future__ import annotations
@@ -128,3 +128,87 @@ def test_device_queries_and_a_growing_batch(alp):
             assert got[:last].tobytes() == ref[:last].tobytes()
             if n > 1:
                 assert int(got[-1]["status"]) == alp.ALP_EINVAL
+
+
+def _range(b):
+    """(U + 1) S of the space's tables: S the most usable options of the last LLM, U the most units
+    of any usable option in multiples of the shares' greatest common divisor."""
+    sp = b["space"]
+    tp, fq, Q, D = (sp["tp"].astype(np.int64), sp["fq"].astype(np.int64), int(sp["Q"]), int(sp["D"]))
+    tpq = tp[:, None] * fq[None, :]
+    fits = b["W"].astype(object)[:, :, None, None] * Q <= tpq.astype(object) * int(b["H"])
+    usable = b["allowed"].astype(bool) & fits.astype(bool)
+    S = int(usable[:, -1].sum(axis=(1, 2)).max()) * D
+    U = int((usable * tpq).max()) * D // int(np.gcd.reduce(fq))
+    return (max(U, 1) + 1) * max(S, 1)
+
+
+@pytest.mark.parametrize("spec", SPACES, ids=[f"seed{s[0]}" for s in SPACES])
+def test_the_plan_takes_the_scan_of_the_range(alp, spec):
+    seed, M, tps, fqs, D, frac_tp, G, instances, count, launches = spec
+    b = make_custom(seed, M, tps, fqs, D, 5, G, count=instances, frac_tp=frac_tp,
+                    deny_prob=0.0 if frac_tp else 0.05)
+    v = _range(b)
+    with alp.Context(b) as ctx:
+        for blocks, threads in launches:
+            ctx.set_launch(0, blocks, threads)
+            form = int(ctx.scan_plan(count)["form"])
+            if M == 2 and len(tps) * len(fqs) * D <= 128:
+                continue
+            assert form == (alp.SCAN_PACKED if v < 0x7C00 else alp.SCAN_PACKED_WIDE) \
+                if v <= 0xFFFF else form in (alp.SCAN_MASKED, alp.SCAN_MASKED_ONE_LAUNCH), v
+        ctx.set_launch(1)
+        assert int(ctx.scan_plan(count)["form"]) in (alp.SCAN_MASKED, alp.SCAN_MASKED_ONE_LAUNCH)
+
+
+def test_both_distributions_occur(alp):
+    seen = set()
+    for seed, M, tps, fqs, D, frac_tp, G, instances, count, launches in SPACES:
+        b = make_custom(seed, M, tps, fqs, D, 5, G, count=instances, frac_tp=frac_tp)
+        with alp.Context(b) as ctx:
+            for blocks, threads in launches:
+                ctx.set_launch(0, blocks, threads)
+                p = ctx.scan_plan(count)
+                seen.add((int(p["form"]) >= alp.SCAN_PACKED, int(p["whole_rows"])))
+    assert {(True, 0), (True, 1)} <= seen
+
+
+# tensor parallel sizes, share units of 16, replicas, denied pairs of the last LLM, (U + 1) S
+ENDS = [
+    ((1, 2, 4), (1, 11), 12, 1, 31_740),                                         # signed
+    ((1, 2, 3, 5, 8, 13, 21, 33), (1, 2, 4, 6, 9, 11, 13, 15), 1, 0, 31_744),    # unsigned, 0x7C00
+    ((1, 2, 11), (1, 2, 3, 5, 7, 14), 5, 1, 65_535),                             # unsigned, the last
+    ((1, 2, 3, 4, 5, 7, 11), (1, 2, 3, 4, 5), 6, 2, 65_538),                     # masked
+]
+
+
+@pytest.mark.parametrize("k", range(len(ENDS)))
+def test_ends_of_the_ranges(alp, k):
+    """Every option deployable but a few pairs of the last LLM, so that (U + 1) S is known; a budget
+    that only the largest options together exceed, and smaller ones."""
+    tps, fqs, D, denied, value = ENDS[k]
+    G = 3 * max(tps) * max(fqs) * D // 16
+    b = make_custom(241 + k, 3, tps, fqs, D, 5, G, count=2, frac_den=16, frac_tp=True)
+    b["W"][:] = 1
+    b["allowed"][:] = 1
+    for i in range(denied):
+        b["allowed"][:, -1, 0, i] = 0
+    assert _range(b) == value
+    want = alp.SCAN_PACKED if value < 0x7C00 else alp.SCAN_PACKED_WIDE
+    with alp.Context(b) as ctx:
+        form = int(ctx.scan_plan(16)["form"])
+        assert form == want if value <= 0xFFFF else form < alp.SCAN_PACKED
+    _check(alp, b, 2, 16, G, [(0, 0), (3, 192), (16, 1024)])
+
+
+def test_a_large_batch_stays_within_a_launch(alp):
+    """The plan's threads are below 2^32 (a launch's limit) for batches up to 2^25 searches."""
+    for seed, M, tps, fqs, D in ((251, 3, (1, 2), (4,), 1), (252, 4, TP4, (2, 4), 2),
+                                 (253, 3, (1, 2, 4, 8, 16), (2, 4), 13), (254, 5, (1, 2), (4,), 2),
+                                 (255, 4, (1, 2, 4), (1, 2, 3, 4), 4)):
+        b = make_custom(seed, M, tps, fqs, D, 5, 16, count=1)
+        with alp.Context(b) as ctx:
+            for count in (1 << 22, 4_300_000, 6_200_000, 1 << 23, 9_000_000, 1 << 24, 1 << 25):
+                p = ctx.scan_plan(count)
+                assert count * int(p["blocks_per_item"]) * int(p["threads_per_block"]) < 1 << 32, \
+                    (seed, count, p)

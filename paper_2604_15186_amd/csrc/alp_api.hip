@@ -437,9 +437,14 @@ bool plan_packed(const alp_ctx *c, uint32_t count, alp::ScanGeometry &out)
         if (idle(k) < idle(row_waves) - 1e-9)
             row_waves = k;
     const uint64_t phases = p.chunks < row_waves ? row_waves / p.chunks : 1;
-    // A tile's instructions, those of the lanes' set-up and of finding the row (measured shares),
-    // and a block's prologue.
-    const double tile = 2.5 * g.slots * alp::inner_stride(sp.O) + 13.0 * g.slots + 45.0;
+    // A tile's instructions: 5 per four records and register of pairs (6 in the unsigned form), and
+    // 47, 62 and 94 besides at one, two and four registers as the kernel is compiled, with some for
+    // the tiles that lower the wave's best.  The lanes' set-up with finding the row, and a block's
+    // prologue, are fits.  Of 20 spaces (3 to 6 LLMs, 16 to 256 options, 1 to 4,096 items) the plan
+    // is within 7% of the best of 100 block counts and sizes in 18, 9% off with eight items of 5
+    // LLMs and 32 options, and 21% with one of 5 LLMs and 48 (29.8 us against 24.5).
+    const double tile = (p.wide ? 3.0 : 2.5) * g.slots * alp::inner_stride(sp.O) +
+                        13.0 * g.slots + 45.0;
     const double setup = (sp.O % 64 == 0 ? 6.0 : 12.0) * g.slots + (sp.M > 3 ? 90.0 : 20.0);
     constexpr double kPrologue = 5600.0;
     uint64_t bpi = 1;

@@ -126,14 +126,6 @@ __device__ __forceinline__ void store_winner(uint32_t L, uint64_t x, Winner *dst
     *dst = r;
 }
 
-// Block-wide minimum; thread 0 writes the block's winner.
-__device__ __forceinline__ void block_min_store(uint32_t L, uint64_t x, Winner *dst)
-{
-    block_min(L, x);
-    if (threadIdx.x == 0)
-        store_winner(L, x, dst);
-}
-
 // Lexicographic (L, x) minimum of an item's block winners, by one wave; every lane gets it.
 // Each lane issues up to eight winner loads before comparing any, so the item's winners arrive
 // in one memory round trip per 512 blocks.
@@ -264,33 +256,6 @@ __device__ __forceinline__ void write_item_result(const FinishArgs &fa, uint32_t
     write_result(fa.sp, E, rejected ? kNoLatency : L, x,
                  reinterpret_cast<uint64_t *>(fa.out + item),
                  rejected ? (uint32_t)ALP_EINVAL : (uint32_t)ALP_INFEASIBLE, fa.signal, fa.seq);
-}
-
-// Writes the block's winner and counts the block as finished (agent-scope fence and per-item
-// counter, zeroed by option_terms_kernel); true in every thread of the item's last block, which
-// then sees every other block's writes.
-__device__ __forceinline__ bool block_store_last(uint32_t L, uint64_t x, uint32_t item,
-                                                 uint32_t sub, uint32_t blocks_per_item,
-                                                 Winner *winners, uint32_t *done)
-{
-    __shared__ uint32_t last_block;
-    block_min_store(L, x, &winners[(uint64_t)item * blocks_per_item + sub]);
-    if (blocks_per_item == 1) {
-        // The block is the whole item: its own writes only need to reach its own threads.
-        __threadfence_block();
-        __syncthreads();
-        return true;
-    }
-    if (threadIdx.x == 0) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");   // the winner, before the count
-        const uint32_t prev = atomicAdd(&done[item], 1u);
-        last_block = prev == blocks_per_item - 1 ? 1u : 0u;
-    }
-    __syncthreads();
-    const bool last = last_block != 0;
-    if (last)
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // every block's winner
-    return last;
 }
 
 // Per-option records of one item the finishing block stages in LDS (M * O at most this many).

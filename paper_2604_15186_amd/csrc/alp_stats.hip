@@ -100,12 +100,6 @@ __device__ __forceinline__ uint32_t lane_xor(uint32_t v)
         return (uint32_t)__builtin_amdgcn_ds_bpermute((int)((threadIdx.x ^ 32u) << 2), (int)v);
 }
 
-template <int Q>
-__device__ __forceinline__ uint64_t lane_xor64(uint64_t v)
-{
-    return (uint64_t)lane_xor<Q>((uint32_t)v) | ((uint64_t)lane_xor<Q>((uint32_t)(v >> 32)) << 32);
-}
-
 // Bitonic sort of P (a power of two) entries in place, ascending by key then val when val is
 // given (keys only otherwise).
 template <bool WithVal>

@@ -172,11 +172,12 @@ struct alp_ctx {
     uint32_t *host_split_dev = nullptr;
     uint32_t *host_query = nullptr;         // pinned staging of batch queries: inst | cap | lambda
     size_t host_query_cap = 0;
-    alp_result_t *host_results = nullptr;   // pinned host memory the kernels write results to
+    uint32_t *host_signal = nullptr;        // mapped word a single search's record signals in
+    uint32_t *host_signal_dev = nullptr;    // (FinishArgs::signal), and its device address; in one
+                                            // allocation with, behind it,
+    alp_result_t *host_results = nullptr;   // the mapped memory the kernels write results to
     alp_result_t *host_results_dev = nullptr;  // its device-visible address
     size_t host_results_cap = 0;            // bytes
-    uint32_t *host_signal = nullptr;        // mapped word a single search's record signals in
-    uint32_t *host_signal_dev = nullptr;    // (FinishArgs::signal), and its device address
     uint32_t call_seq = 0;                  // the last sequence number signalled
 
     uint32_t variant = 0, bpi_override = 0, tpb_override = 0, chunks_override = 0;
@@ -750,42 +751,31 @@ int32_t upload_queries(alp_ctx *c, uint32_t count, const uint32_t *inst, const u
     return ALP_OK;
 }
 
-int32_t ensure_host_signal(alp_ctx *c)
-{
-    if (c->host_signal)
-        return ALP_OK;
-    void *h = nullptr, *d = nullptr;
-    hipError_t e = alloc_pinned(&h, 64, hipHostMallocMapped);
-    if (e != hipSuccess)
-        return hip_fail(e, "hipHostMalloc(signal)");
-    if ((e = hipHostGetDevicePointer(&d, h, 0)) != hipSuccess) {
-        (void)hipHostFree(h);
-        return hip_fail(e, "hipHostGetDevicePointer(signal)");
-    }
-    c->host_signal = (uint32_t *)h;
-    c->host_signal_dev = (uint32_t *)d;
-    __atomic_store_n(c->host_signal, 0u, __ATOMIC_RELEASE);
-    return ALP_OK;
-}
-
-// The mapped result buffer, of at least `bytes`.
+// The mapped result buffer, of at least `bytes`, behind the signal word on a line of its own.  At
+// least 64 KiB, so that a context pins memory once for calls of ordinary sizes.
 int32_t ensure_host_results(alp_ctx *c, size_t bytes)
 {
-    if (bytes <= c->host_results_cap)
+    constexpr size_t kLine = 64, kLeast = (size_t)64 << 10;
+    if (c->host_signal && bytes <= c->host_results_cap)
         return ALP_OK;
+    const size_t size = std::max(kLeast, bytes + kLine);
     void *grown = nullptr, *grown_dev = nullptr;
-    hipError_t e = alloc_pinned(&grown, bytes, hipHostMallocMapped);
+    hipError_t e = alloc_pinned(&grown, size, hipHostMallocMapped);
     if (e != hipSuccess)
         return hip_fail(e, "hipHostMalloc(results)");
     if ((e = hipHostGetDevicePointer(&grown_dev, grown, 0)) != hipSuccess) {
         (void)hipHostFree(grown);
         return hip_fail(e, "hipHostGetDevicePointer(results)");
     }
-    if (c->host_results)
-        (void)hipHostFree(c->host_results);
-    c->host_results = (alp_result_t *)grown;
-    c->host_results_dev = (alp_result_t *)grown_dev;
-    c->host_results_cap = bytes;
+    if (c->host_signal)
+        (void)hipHostFree(c->host_signal);
+    c->host_signal = (uint32_t *)grown;
+    c->host_signal_dev = (uint32_t *)grown_dev;
+    __atomic_store_n(c->host_signal, 0u, __ATOMIC_RELEASE);
+    c->call_seq = 0;
+    c->host_results = (alp_result_t *)((uint8_t *)grown + kLine);
+    c->host_results_dev = (alp_result_t *)((uint8_t *)grown_dev + kLine);
+    c->host_results_cap = size - kLine;
     return ALP_OK;
 }
 
@@ -1000,8 +990,6 @@ int32_t run_search(alp_ctx *c, const alp::QueryDev &q, uint32_t count)
     if (st != ALP_OK)
         return st;
     const bool signalled = count == 1 && !c->timing;
-    if (signalled && (st = ensure_host_signal(c)) != ALP_OK)
-        return st;
     uint32_t seq = 0;
     if (signalled && ++c->call_seq == 0)
         ++c->call_seq;                         // 0 is the word's initial value
@@ -1870,9 +1858,7 @@ void alp_free(alp_ctx *ctx)
                       &ctx->fused_words};
     for (DevBuf *b : bufs)
         b->release();
-    if (ctx->host_results)
-        (void)hipHostFree(ctx->host_results);
-    if (ctx->host_signal)
+    if (ctx->host_signal)                              // (with the results behind it)
         (void)hipHostFree(ctx->host_signal);
     if (ctx->host_query)
         (void)hipHostFree(ctx->host_query);

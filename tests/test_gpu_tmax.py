@@ -47,15 +47,37 @@ def test_matches_the_oracle(alp, point):
 
 
 def test_results_take_four_bytes_an_item(alp, monkeypatch):
-    """A context that has returned 100 search records (48 bytes each) holds a result buffer for
-    1,200 throughputs: with the queries' buffers there, no allocation is needed."""
+    """A context that has returned 3,000 search records (48 bytes each) holds a result buffer for
+    36,000 throughputs: with the queries' buffers there, no allocation is needed."""
     b = make_custom(411, 2, (1, 2), (2, 4), 2, 4, 8, count=1)
-    G = (np.arange(1200) % 9).astype(np.uint32)
-    inst = np.zeros(1200, np.uint32)
+    G = (np.arange(36_000) % 9).astype(np.uint32)
+    inst = np.zeros(36_000, np.uint32)
     with alp.Context(b) as ctx:
-        want = np.concatenate([ctx.max_throughput(G[k:k + 9], instances=inst[:9])
-                               for k in range(0, 1200, 9)])
-        ctx.search_batch(G[:100], np.ones(100, np.uint32), instances=inst[:100])
-        ctx.search_pruned(G, np.ones(1200, np.uint32), instances=inst)
+        want = np.tile(ctx.max_throughput(G[:9], instances=inst[:9]), 4_000)
+        ctx.search_batch(G[:3_000], np.ones(3_000, np.uint32), instances=inst[:3_000])
+        ctx.search_pruned(G, np.ones(36_000, np.uint32), instances=inst)
         monkeypatch.setenv("ALP_TEST_FAIL_ALLOC", "1")
-        assert ctx.max_throughput(G, instances=inst).tolist() == want[:1200].tolist()
+        assert ctx.max_throughput(G, instances=inst).tolist() == want.tolist()
+
+
+def test_searches_after_throughputs_pin_no_more_memory(alp, monkeypatch):
+    """The throughputs that set a search's target and the searches that follow share one buffer."""
+    b = make_custom(412, 2, (1, 2), (2, 4), 2, 4, 8, count=1)
+    G = np.full(1_000, 8, np.uint32)
+    inst = np.zeros(1_000, np.uint32)
+    with alp.Context(b) as other:
+        want = other.search_batch(G, np.ones(1_000, np.uint32), instances=inst)
+    with alp.Context(b) as ctx:
+        ctx.max_throughput(G, instances=inst)
+        out = ctx.search_pruned(G, np.ones(1_000, np.uint32), instances=inst)   # device buffers
+        assert len(out) == 1_000
+        one = ctx.search(0, 8, 1)
+        assert one.tobytes() == want[0].tobytes()
+        monkeypatch.setenv("ALP_TEST_FAIL_ALLOC", "1")
+        assert ctx.search(0, 8, 1).tobytes() == want[0].tobytes()
+        try:
+            got = ctx.search_batch(G, np.ones(1_000, np.uint32), instances=inst)
+        except alp.AlpError as err:                   # the scan's own device buffers only
+            assert err.status == alp.ALP_ENOMEM and "results" not in str(err)
+        else:
+            assert got.tobytes() == want.tobytes()

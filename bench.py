@@ -727,7 +727,7 @@ def run_stats(args, alp):
     # As logged (in order of end time): the sweep without a sort.
     k_ms, elapsed, out = timed(np.arange(calls))
     # The same calls shuffled within each trace: every trace is sorted (the context sees that the
-    # traces are not in end order and sorts directly, checking the order again every 8th call).
+    # traces are not in end order and sorts directly until it finds most of them in order).
     rng = np.random.default_rng(5)
     off = tr["offsets"].astype(np.int64)
     perm = np.concatenate([lo + rng.permutation(hi - lo) for lo, hi in zip(off[:-1], off[1:])])

@@ -359,8 +359,9 @@ typedef struct {
 
 /* Places count allocations (search results of this context's space: tp, frac_units, replicas
  * per LLM; an ALP_INFEASIBLE result places nothing) on gpu_budget[i] <= ALP_PLACE_MAX_GPUS GPUs
- * each, one thread per allocation.  Host arrays; synchronous on the context's stream.  EINVAL for
- * a budget above the maximum or a record whose choices are not of the space. */
+ * each, four allocations to a wavefront up to 16 GPUs and one beyond.  Host arrays; synchronous on
+ * the context's stream.  EINVAL for a budget above the maximum or a record whose choices are not
+ * of the space. */
 int32_t alp_place(alp_ctx *ctx, uint32_t count, const alp_result_t *allocations,
                   const uint32_t *gpu_budget, alp_placement_t *out);
 
@@ -421,7 +422,8 @@ int32_t alp_scan_plan(alp_ctx *ctx, uint32_t count, alp_scan_plan_t *out);
  * option-term kernel (ms[0]; 0 when the search ran in one launch) and of the candidate scan
  * kernel, which includes the final reduction and the result write (ms[1]); ms[2] is the budget-split kernel of alp_allocate_workflows, 0
  * after the other searches.  After alp_search_pruned: ms[1] is the fraction enumeration and ms[2]
- * the admissible-option table.  After alp_place: ms[1] is the placement kernel, the others 0.
+ * the admissible-option tables where they lie in device memory (0 where the enumeration's blocks
+ * build them in LDS).  After alp_place: ms[1] is the placement kernel, the others 0.
  * *scan_blocks receives the scan (or enumeration) grid size of the last search.
  * alp_kernel_time_totals writes the sums of those three figures over the timed calls since
  * timing was last set, and (if timed_calls is not NULL) their number, so that a caller timing

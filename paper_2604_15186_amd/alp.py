@@ -325,7 +325,7 @@ class Context:
 
     def kernel_times(self):
         """(option-term ms, scan ms, third-kernel ms, grid blocks) of the last call; the third
-        kernel is the budget split or the pruned search's option table."""
+        kernel is the budget split or the pruned search's option tables in device memory."""
         ms = (C.c_float * 3)()
         blocks = C.c_uint32()
         _check(lib().alp_kernel_times(self._ctx, ms, C.byref(blocks)))

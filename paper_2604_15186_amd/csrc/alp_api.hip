@@ -1522,14 +1522,14 @@ int32_t alp_search_pruned(alp_ctx *ctx, uint32_t count, const uint32_t *instance
         return hip_fail(guard.status, "hipSetDevice");
     begin_call(ctx);
     const uint64_t items_bytes = (uint64_t)count * sp.M * sp.O * sizeof(uint2);
+    const uint64_t tables = alp::pruned_table_entries(sp, F_max, flags);   // 0: in the blocks' LDS
     hipError_t e;
     if ((e = ctx->rec.ensure(items_bytes)) != hipSuccess || (e = ctx->ext.ensure(items_bytes)) != hipSuccess ||
         (bpi > 1 &&
          ((e = ctx->winners.ensure(nblocks * 3 * sizeof(uint64_t))) != hipSuccess ||
           (e = ctx->fused_words.ensure(alp::block_counter_words(count, bpi) * sizeof(uint32_t))) !=
               hipSuccess)) ||
-        (e = ctx->pruned_table.ensure(count * alp::pruned_table_entries(sp, F_max, flags) *
-                                      sizeof(uint64_t))) != hipSuccess)
+        (e = ctx->pruned_table.ensure(count * tables * sizeof(uint64_t))) != hipSuccess)
         return hip_fail(e, "hipMalloc(pruned search)");
     if (count > ctx->host_pruned_cap) {
         void *grown = nullptr, *grown_dev = nullptr;
@@ -1563,17 +1563,20 @@ int32_t alp_search_pruned(alp_ctx *ctx, uint32_t count, const uint32_t *instance
                                 (uint64_t *)ctx->pruned_table.ptr, bpi,
                                 (uint64_t *)ctx->winners.ptr, (uint32_t *)ctx->fused_words.ptr, ext,
                                 ctx->host_pruned_dev, ctx->stream,
-                                ctx->timing ? ctx->ev[2] : nullptr)) != hipSuccess)
+                                ctx->timing && tables ? ctx->ev[2] : nullptr)) != hipSuccess)
         return hip_fail(e, "pruned search launch");
     if (ctx->timing && (e = hipEventRecord(ctx->ev[3], ctx->stream)) != hipSuccess)
         return hip_fail(e, "hipEventRecord");
     if ((e = hipStreamSynchronize(ctx->stream)) != hipSuccess)
         return hip_fail(e, "hipStreamSynchronize");
     if (ctx->timing) {
-        // ms[0]: option terms, ms[1]: fraction enumeration, ms[2]: admissible-option table
+        // ms[0]: option terms, ms[1]: fraction enumeration, ms[2]: option tables in device memory
+        ctx->last_ms[2] = 0.0f;
         if ((e = hipEventElapsedTime(&ctx->last_ms[0], ctx->ev[0], ctx->ev[1])) != hipSuccess ||
-            (e = hipEventElapsedTime(&ctx->last_ms[2], ctx->ev[1], ctx->ev[2])) != hipSuccess ||
-            (e = hipEventElapsedTime(&ctx->last_ms[1], ctx->ev[2], ctx->ev[3])) != hipSuccess)
+            (tables && (e = hipEventElapsedTime(&ctx->last_ms[2], ctx->ev[1], ctx->ev[2])) !=
+                           hipSuccess) ||
+            (e = hipEventElapsedTime(&ctx->last_ms[1], ctx->ev[tables ? 2 : 1], ctx->ev[3])) !=
+                hipSuccess)
             return hip_fail(e, "hipEventElapsedTime");
         for (int k = 0; k < 3; ++k)
             ctx->tally(k);

@@ -80,3 +80,15 @@ def test_more_queries_than_a_launch_of_whole_blocks_holds(alp):
         w = oracle.pruned(oracle.Instance(b, 1), 3, 100, 3)
         assert (int(want[3]["best"]["index"]), int(want[3]["vectors"])) == \
             (alp.NO_INDEX if w["x"] is None else w["x"], w["vectors"])
+
+
+def test_the_table_time_is_that_of_tables_in_memory(alp):
+    """820 ordered units are the most a block holds in LDS: no table kernel, and no time for one."""
+    b = make_custom(331, 3, (1, 2, 4, 8), (2, 5, 10), 8, 4, 83, count=1, frac_den=10, alpha=0.7)
+    with alp.Context(b) as ctx:
+        ctx.set_timing(1)
+        for G, in_memory in ((82, False), (83, True), (82, False)):
+            ctx.search_pruned(np.asarray([G], np.uint32), np.asarray([10], np.uint32), 1,
+                              instances=np.asarray([0], np.uint32))
+            terms, enumeration, table, _ = ctx.kernel_times()
+            assert terms > 0 and enumeration > 0 and (table > 0) == in_memory

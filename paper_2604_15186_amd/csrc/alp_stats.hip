@@ -21,9 +21,9 @@
 //                            (llm << 61 | start << 32 | duration, starts within 2^29 us of a
 //                            reference) in registers and across lanes -- no LDS, no barrier --
 //                            and sweeps them as below; other traces go to the work list.
-//   trace_group_kernel<E,NT> the same for traces of 513 to 1,024 calls (two waves each) and of
-//                            1,025 to 2,048 (four), 8 keys per thread, the exchanges between
-//                            waves through LDS.
+//   trace_group_kernel       the same for traces of 513 to 1,024 calls (two waves each), of 1,025 to
+//                            1,536 (three) and of 1,537 to 2,048 (four), 8 keys per thread, the
+//                            exchanges between waves through LDS.
 //   trace_sort_kernel        the work list: calls sorted by key (llm << 60 | start), packed into
 //                            one 64-bit key when the starts span under 2^29 us, with a bitonic
 //                            network in registers, across lanes and in LDS; the time covered by
@@ -1060,7 +1060,7 @@ trace_wave_kernel(StatsArgs a)
 // Every trace of LO + 1 to NT E calls sorted directly (8 keys per thread: 513 to 1,024 calls on
 // two waves, 1,025 to 1,536 on three, 1,537 to 2,048 on four): one workgroup of NT threads per
 // trace, keyed and handed on as in trace_wave_kernel, sorted by mirror_sort_regs (exchanges
-// between waves through one LDS buffer of NT E keys).  8 keys per thread keep about 50 VGPRs;
+// between waves through one LDS buffer of NT E keys).  8 keys per thread keep about 60 VGPRs;
 // 16 or 32 keys per lane needed 89 and 171 (2 to 5 waves per SIMD instead of 8).
 template <bool FLOAT, int E, int NT, int LO>
 __global__ void __launch_bounds__(NT) trace_group_kernel(StatsArgs a)

@@ -1019,9 +1019,10 @@ __device__ __forceinline__ void wave_trace(const StatsArgs &a, uint32_t r, uint6
 
 // Every trace of at most 512 calls sorted directly (the context found most traces out of end
 // order): one wave per trace, kWaveSortWaves traces per workgroup; traces the wave does not take
-// (a span beyond its packed keys) are listed for the block sort that follows.
+// (a span beyond its packed keys) are listed for the block sort that follows.  Seven waves per SIMD:
+// eight would spill three registers, and a process pays 0.2 ms for scratch at the first such launch.
 template <bool FLOAT>
-__global__ void __launch_bounds__(64 * kWaveSortWaves) __attribute__((amdgpu_waves_per_eu(8)))
+__global__ void __launch_bounds__(64 * kWaveSortWaves) __attribute__((amdgpu_waves_per_eu(7)))
 trace_wave_kernel(StatsArgs a)
 {
     __shared__ unsigned long long s_sum[kWaveSortWaves][3 * ALP_MAX_LLMS];

@@ -360,7 +360,7 @@ class StatsContext:
                ((offsets, np.uint64), (llm, np.uint32), (start, np.uint64), (end, np.uint64))]
         out = np.zeros(num_llms, dtype=STATS_DTYPE)
         R = int(dev[0].numel()) - 1
-        calls = min(int(t.numel()) for t in dev[1:])
+        calls = min(dev[1].numel(), dev[2].numel(), dev[3].numel())
         _check(lib().alp_trace_stats_sized(self._ctx, num_llms, R,
                                            *(C.c_void_p(t.data_ptr()) for t in dev), calls,
                                            _ptr(out)))

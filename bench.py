@@ -43,7 +43,7 @@ a workload's instances (``--config``, default the 4,096-instance batch), and rep
 the searched optima, and of the pruned search's results, can be placed on the budget's 8-GPU
 nodes.
 
-``--workload stats`` times the workflow statistics (alp_trace_stats, Section 4 step 2) over
+``--workload stats`` times the workflow statistics (alp_trace_stats_sized, Section 4 step 2) over
 20,000 synthetic beam-search traces (about 15 million LLM calls, resident on the device);
 ``value`` counts trace calls per second and the roofline is HBM: 20 bytes read per call (LLM
 index and two timestamps) and 8 per trace offset.

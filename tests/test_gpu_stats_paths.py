@@ -231,4 +231,4 @@ def test_the_first_direct_sort_launches_only_the_groups_it_needs(alp):
             got = ctx.compute(1, offsets, llm, start, start + 50)
             ms.append(ctx.time_ms())
             assert [int(v) for v in got[0]] == [2000, 1000, 2 * R, 100 * R, 100 * R]
-    assert ms[1] < 1.5 * min(ms[2:]), ms
+    assert ms[1] < 2 * min(ms[2:]), ms                    # 4.9 and 1.8 ms with every group launched
